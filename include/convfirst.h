@@ -286,37 +286,26 @@ cf_status cf_stem_gblock_forward(const void *x, void *y, const cf_stem_params *s
  *   (NULL scale means 1, NULL bias 0; folded batch norms go into the s/b pairs)
  * Each work item (an image and 64 of its hidden channels) computes its
  * expand and conv layers alone; the squeeze sums over every hidden channel
- * and the projection reads all of them, so the work items of an image
- * exchange their conv outputs and squeeze shares through ws and meet once in
- * global memory.  The kernel is therefore launched cooperatively, with each
- * image's work items resident together.  The target is the late stages of a
- * network: supported are k = 3, 1 <= H, W <= 16, C a multiple of 16, E*C a
- * multiple of 64 and at most 4096, 1 <= R <= 256, and a shared-memory layout
- * (the group's W1 rows, the gates of all E*C channels, the staged hidden
- * layer) within the 160 KB of a CU: C up to 768 at E = 2, 512 at E = 4, 256
- * at E = 8 (CF_ERR_UNSUPPORTED otherwise; C not a multiple of 8 is
- * CF_ERR_INVALID).  y may equal x
- * (evaluation in place); any other overlap among x, y and ws is
- * CF_ERR_INVALID.  ws: cf_mbconv_workspace_bytes() bytes (queried on the
- * current device) let every image the device can hold be in flight; a
- * smaller ws runs fewer images at once, and one too small for a single image
- * returns CF_ERR_WORKSPACE.  ws must be zero-filled before its first use:
- * its first 256 + 2048 * 128 bytes hold the barrier lines of the images in
- * flight, and every call leaves them zero again, whatever the shapes of the
- * calls that share the workspace, so a call is a single launch.  If a
- * barrier wait ever gives up (that call's output is then invalid; the
- * cooperative launch rules this out), the first int of ws is set to 1 and the
- * library never clears it.  Calls that share a workspace must not overlap in
- * time.
- * launch: CF_LAUNCH_COOPERATIVE (hipLaunchCooperativeKernel: the runtime
- * makes every workgroup resident at once, and refuses a grid that cannot be)
- * or CF_LAUNCH_EXCLUSIVE, an ordinary launch of the same grid (sized to what
- * fits on the device) for callers that own the device for the call -- no
- * kernel of theirs or anyone else's runs beside it.  It saves the cooperative
- * launch's fixed cost (about 17 us per call measured on MI355X); if other
- * work does keep a workgroup from starting, a wait gives up after about a
- * second and the flag above is set (the kernel still ends).  fp16 or bf16 I/O, fp32
- * accumulation; U, V and the gated project weights are rounded to the I/O
+ * and the projection reads all of them, so the block runs as two ordinary
+ * launches that exchange the conv output and the squeeze shares through ws.
+ * The target is the late stages of a network: supported are k = 3,
+ * 1 <= H, W <= 16, C a multiple of 16, E*C a multiple of 64 and at most 4096,
+ * 1 <= R <= 256, and the size rule of the kernel source (the group's W1 rows,
+ * the gates of all E*C channels, the staged hidden layer within 160 KB): C up
+ * to 768 at E = 2, 512 at E = 4, 256 at E = 8 (CF_ERR_UNSUPPORTED otherwise;
+ * C not a multiple of 8 is CF_ERR_INVALID).  y may equal x (evaluation in
+ * place); any other overlap among x, y and ws is CF_ERR_INVALID.  ws:
+ * cf_mbconv_workspace_bytes() bytes hold the conv output of the whole batch,
+ * or of as many images as fit 128 MiB (the rest follow in further launch
+ * pairs); a smaller ws runs fewer images per pair, and one too small for two
+ * images returns CF_ERR_WORKSPACE.  Its first 256 + 2048 * 128 bytes are
+ * reserved and left as they are (a ws zeroed before its first use stays
+ * zero there; no call needs it zeroed).  Calls that share a workspace must
+ * not overlap in time.
+ * launch: CF_LAUNCH_COOPERATIVE and CF_LAUNCH_EXCLUSIVE are both accepted and
+ * launch alike: no kernel waits for another workgroup, so neither a
+ * cooperative launch nor a device of one's own is needed.  fp16 or bf16 I/O,
+ * fp32 accumulation; U, V and the gated conv output are rounded to the I/O
  * dtype before their products.  Deterministic: every sum has a fixed order. */
 typedef struct {
     const void *w1;
@@ -361,7 +350,7 @@ size_t cf_mbconv_workspace_bytes(int N, int H, int W, int C, int E, int R, cf_dt
  * differ); ws as for cf_mbconv_forward, sized by
  * cf_mbconv_s2_workspace_bytes (the exchanged map is V', a quarter of V).
  * Each work item blurs its own 64 channels from its LDS copy of V before the
- * exchange, so the block is still one launch with one barrier per image.
+ * exchange.
  * V and V' are rounded to the I/O dtype (V' sums 9 rounded V values in fp32);
  * the squeeze sums the unrounded fp32 V'.  Deterministic. */
 cf_status cf_mbconv_s2_forward(const void *x, void *y, void *ws, size_t ws_bytes, const cf_mbconv_params *p,

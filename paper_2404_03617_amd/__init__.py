@@ -577,15 +577,15 @@ _MBCONV_SHAPES = {
 
 
 def mbconv_workspace_bytes(N: int, H: int, W: int, C: int, E: int, R: int, dtype=torch.float16) -> int:
-    """Recommended workspace of mbconv_forward on the current device (0 for a
-    shape without a kernel)."""
+    """Recommended workspace of mbconv_forward (0 for a shape without a
+    kernel)."""
     return int(lib().cf_mbconv_workspace_bytes(N, H, W, C, E, R, DTYPES[dtype]))
 
 
 def mbconv_s2_workspace_bytes(N: int, H: int, W: int, C: int, E: int, R: int, K: int,
                               dtype=torch.float16) -> int:
-    """Recommended workspace of mbconv_s2_forward on the current device (0 for
-    a shape without a kernel)."""
+    """Recommended workspace of mbconv_s2_forward (0 for a shape without a
+    kernel)."""
     return int(lib().cf_mbconv_s2_workspace_bytes(N, H, W, C, E, R, K, DTYPES[dtype]))
 
 
@@ -629,21 +629,20 @@ def _mbconv_args(x: torch.Tensor, p: dict, launch: str, stride2: bool):
 
 def mbconv_forward(x: torch.Tensor, p: dict, out=None, ws=None, launch: str = "cooperative",
                    stream=None) -> torch.Tensor:
-    """The paper's MBConv block with Squeeze & Excitation (Sec. 5.4) fused
-    into one cooperative kernel (Sec. 5.4.1).  p holds w1 [E*C,C], gw_w
+    """The paper's MBConv block with Squeeze & Excitation (Sec. 5.4), fused
+    into two launches cut at the squeeze.  p holds w1 [E*C,C], gw_w
     [3,3,E*C,8], wr [R,E*C], we [E*C,R], w2 [C,E*C] in x's dtype and optional
     fp32 s1,b1,s2,b2,be [E*C], br [R], s3,b3 [C].  out may be x itself
-    (evaluation in place).  ws: a uint8 workspace, by default a zeroed one of
-    mbconv_workspace_bytes(); a smaller one runs fewer images at a time.  A
-    caller's ws must be zeroed before its first use (every call leaves it
-    reusable); its first int32 becomes 1 if a barrier wait ever gave up.
-    launch="exclusive" replaces the cooperative launch by an ordinary one,
-    for callers that own the device (see the C header)."""
+    (evaluation in place).  ws: a uint8 workspace, by default one of
+    mbconv_workspace_bytes(); a smaller one runs fewer images at a time.
+    launch: "cooperative" and "exclusive" launch alike (see the C header)."""
     (N, H, W, C, E, R, _, k), mp, keep = _mbconv_args(x, p, launch, False)
     y = _out(x, out)
     if ws is None:
-        ws = torch.zeros(max(1, mbconv_workspace_bytes(N, H, W, C, E, R, x.dtype)), dtype=torch.uint8,
+        ws = torch.empty(max(1, mbconv_workspace_bytes(N, H, W, C, E, R, x.dtype)), dtype=torch.uint8,
                          device=x.device)
+        if stream is not None:
+            ws.record_stream(stream)  # freed here, in use there
     else:
         _workspace(x, ws, 0)
     _check(lib().cf_mbconv_forward(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), ctypes.byref(mp), N, H, W, C, E,
@@ -663,8 +662,10 @@ def mbconv_s2_forward(x: torch.Tensor, p: dict, out=None, ws=None, launch: str =
     (N, H, W, C, E, R, K, k), mp, keep = _mbconv_args(x, p, launch, True)
     y = _out(x, out, (N, (H + 1) // 2, (W + 1) // 2, K))
     if ws is None:
-        ws = torch.zeros(max(1, mbconv_s2_workspace_bytes(N, H, W, C, E, R, K, x.dtype)), dtype=torch.uint8,
+        ws = torch.empty(max(1, mbconv_s2_workspace_bytes(N, H, W, C, E, R, K, x.dtype)), dtype=torch.uint8,
                          device=x.device)
+        if stream is not None:
+            ws.record_stream(stream)  # freed here, in use there
     else:
         _workspace(x, ws, 0)
     _check(lib().cf_mbconv_s2_forward(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), ctypes.byref(mp), N, H, W, C, E,

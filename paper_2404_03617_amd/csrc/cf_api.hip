@@ -260,10 +260,7 @@ size_t mbconv_ws(int N, int H, int W, int C, int E, int R, int K, cf_dtype dt) {
     if (N <= 0 || E <= 0 || (double)E * C > 65536.0 || !cf::mbconv_supported(H, W, C, E, R, K) ||
         ((int)dt != CF_F16 && (int)dt != CF_BF16))
         return 0;
-    int slots = 0;
-    if (cf::mbconv_resident_slots(H, W, C, E, R, K, dt == CF_BF16, &slots) != hipSuccess || slots < 1)
-        slots = 1;
-    return cf::mbconv_workspace_bytes(N, H, W, C, E, R, K, slots < N ? slots : N);
+    return cf::mbconv_workspace_bytes(N, H, W, C, E, R, K, cf::mbconv_images_in_flight(N, H, W, C, E, K));
 }
 
 cf_status mbconv_call(const char *what, const void *x, void *y, void *ws, size_t ws_bytes, const cf_mbconv_params *p,
@@ -304,7 +301,7 @@ cf_status mbconv_call(const char *what, const void *x, void *y, void *ws, size_t
                     "%s: no kernel for H=%d W=%d C=%d E=%d R=%d K=%d (supported: H, W <= 16, C %% 16 == 0, "
                     "E*C %% 64 == 0, E*C <= 4096, R <= 256, K %% 16 == 0)",
                     what, H, W, C, E, R, K);
-    const size_t need = cf::mbconv_workspace_bytes(N, H, W, C, E, R, K, 1);
+    const size_t need = cf::mbconv_workspace_bytes(N, H, W, C, E, R, K, 2);
     if (!ws || ws_bytes < need)
         return fail(CF_ERR_WORKSPACE, "%s: ws has %zu bytes, needs at least %zu", what, ws ? ws_bytes : (size_t)0,
                     need);
@@ -325,10 +322,7 @@ cf_status mbconv_call(const char *what, const void *x, void *y, void *ws, size_t
     w.s3 = p->s3;
     w.b3 = p->b3;
     hipError_t e = cf::launch_mbconv(x, y, w, N, H, W, C, E, R, K, dt == CF_BF16, ws, ws_bytes,
-                                     launch == CF_LAUNCH_COOPERATIVE, (hipStream_t)stream);
-    if (e == hipErrorInvalidConfiguration)
-        return fail(CF_ERR_UNSUPPORTED, "%s: the %d work items of one image do not fit on the device at once", what,
-                    E * C / 64);
+                                     (hipStream_t)stream);
     if (e != hipSuccess)
         return hip_fail(e, what);
     g_err[0] = 0;

@@ -161,16 +161,16 @@ struct MBConvW {
 // Shapes with a kernel: H, W <= 16 (>= 2 for stride 2), C % 16 == 0,
 // E*C % 64 == 0, E*C <= 4096, 1 <= R <= 256, K % 16 == 0.
 bool mbconv_supported(int H, int W, int C, int E, int R, int K = 0);
-// Images the device can hold in flight at once (all their work items resident).
-hipError_t mbconv_resident_slots(int H, int W, int C, int E, int R, int K, int bf16, int *slots);
-// Workspace bytes for `slots` images in flight.
-size_t mbconv_workspace_bytes(int N, int H, int W, int C, int E, int R, int K, int slots);
-// Fused MBConv block; ws of ws_bytes >= mbconv_workspace_bytes(..., 1)
-// (hipErrorInvalidValue otherwise), its header zero.  The first int of ws is
-// set if a barrier wait gave up.  coop: hipLaunchCooperativeKernel, else an
-// ordinary launch of the same grid.
+// Workspace bytes with room for the exchanged maps of `images` images (at
+// least 2).
+size_t mbconv_workspace_bytes(int N, int H, int W, int C, int E, int R, int K, int images);
+// Images the recommended workspace holds.
+int mbconv_images_in_flight(int N, int H, int W, int C, int E, int K);
+// MBConv block, two launches per pass over as many images as the workspace
+// holds; ws of ws_bytes >= mbconv_workspace_bytes(..., 2) (hipErrorInvalidValue
+// otherwise).  Its header stays untouched.
 hipError_t launch_mbconv(const void *x, void *y, const MBConvW &w, int N, int H, int W, int C, int E, int R, int K,
-                         int bf16, void *ws, size_t ws_bytes, bool coop, hipStream_t st);
+                         int bf16, void *ws, size_t ws_bytes, hipStream_t st);
 
 // Upper bound of dynamic LDS the fused kernel needs for this shape (bytes);
 // 0 when no kernel configuration fits.

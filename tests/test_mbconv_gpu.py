@@ -181,3 +181,24 @@ def test_mbconv_workspace_reused_across_calls():
             torch.cuda.synchronize()
             assert barrier_flag(ws) == 0
             assert torch.equal(y, cf.mbconv_forward(xd, pd))
+
+
+@pytest.mark.parametrize("case", [(16, 4, 4), (128, 2, 32), (144, 4, 36), (272, 4, 200), (64, 3, 20)],
+                         ids=lambda c: "C%d_E%d_R%d" % c)
+def test_mbconv_many_tiles_cover_every_output_split(case):
+    """Enough images that a projection workgroup covers every output channel:
+    one to four 16-channel tiles per wave, a second group of output tiles
+    (C = 272), a last chunk of E*C that is not full, R not a multiple of 8;
+    and a workspace for 7 images at a time gives the same bits."""
+    C, E, R = case
+    N, H, W = 36, 16, 15
+    say("mbconv many tiles", case)
+    x, p = make(95, N, H, W, C, E, R)
+    y, _ = run(x, p)
+    pick = [0, 6, 7, 20, 35]
+    assert_close(y.cpu()[pick], ref(x[pick], p), what="mbconv %s" % (case,), diag=DIAG_F16)
+    fixed = 256 + 2048 * 128 + (N * (E * C // 64) * R * 4 + 255) // 256 * 256
+    ws = torch.empty(fixed + 7 * H * W * E * C * 2, dtype=torch.uint8, device="cuda")
+    y7 = cf.mbconv_forward(x.cuda(), to_dev(p), ws=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(y7, y)
