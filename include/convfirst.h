@@ -89,8 +89,9 @@ typedef struct {
 /* One ConvFirst block, fused (Sec. 5.3.1, eq. e:ffn-eff): y = block(x).
  * x, y: [N][H][W][C].  Supported: C in {64, 128, 256, 512}, E >= 1,
  * k in {1, 3, 5, 7}; any N, H, W >= 1.  Other C return CF_ERR_UNSUPPORTED.
- * With N*H*W <= 64 and C >= 128 the block runs on one workgroup per 32
- * output channels (each recomputing the expand, no workspace; Sec. 4.1.2:
+ * One launch, or two for C = 256, 512 and C = 128 in bf16 (the depth-wise
+ * output passes through y).  With N*H*W <= 64 and C >= 128 the block runs on
+ * one workgroup per 32 output channels (each recomputing the expand, no workspace; Sec. 4.1.2:
  * the weights are the bytes), unless the autotuner cached another
  * configuration for the shape. */
 cf_status cf_block_forward(const void *x, void *y, const cf_block_params *p,
@@ -102,8 +103,9 @@ cf_status cf_block_forward(const void *x, void *y, const cf_block_params *p,
  * y and ws; blocks[depth] are host-side structs of device pointers.
  * cf_stage_workspace_bytes() returns the recommended ws size.  The minimum is
  * N*H*W*C*2 bytes (rounded up to 256) for depth > 1 and 0 for depth == 1;
- * for C = 512 fp16 the recommended size adds 16*N*H*W*C bytes.  With that
- * room, at N*H*W >= 4096 pixels and E <= 6, each block runs layer by layer
+ * for C = 512 fp16 the recommended size adds 16*N*H*W*C bytes, for C = 256
+ * over at most 4096 pixels up to 32*N*H*W*C (16 MiB at most).  With that
+ * room, at C = 512 fp16, N*H*W >= 4096 pixels and E <= 6, each block runs layer by layer
  * (Sec. 5.2): a depth-wise kernel, the expand and project as hipBLASLt
  * GEMMs with the hidden tensor in ws (s1, b1 and the activation in the
  * expand's epilogue, with the library's GELU, when s1 and b1 are given;
@@ -111,8 +113,10 @@ cf_status cf_block_forward(const void *x, void *y, const cf_block_params *p,
  * project's epilogue (else an elementwise kernel after it, the project's
  * output rounded to fp16 first); within the block tolerance of the fused
  * kernels, deterministic.
- * Otherwise, with the room, each block splits its hidden layer over several
- * workgroups (results identical up to fp32 summation order, deterministic).
+ * Otherwise, at C = 256 and 512 over few pixels, each block splits its hidden
+ * layer over as many groups of workgroups as the room behind the minimum holds
+ * (4*N*H*W*C bytes a group; a larger ws than recommended is used as well).
+ * Results identical up to fp32 summation order, deterministic.
  * The library GEMMs are given no workspace of their own. */
 cf_status cf_stage_forward(const void *x, void *y, void *ws, size_t ws_bytes,
                            const cf_block_params *blocks, int depth,
@@ -130,8 +134,8 @@ size_t cf_stage_workspace_bytes(int depth, int N, int H, int W, int C, cf_dtype 
  * micro-batch whose activations fit the L2s is read back from them; one that
  * fits the 256 MiB Infinity Cache is read back from it.  Only the stage's
  * input and output need DRAM.  Results equal cf_stage_forward's up to the
- * fp32 summation order of the hidden split it may use at C = 512 (none
- * here).  micro_batch <= 0 picks a default: the largest micro-batch whose
+ * fp32 summation order of the hidden split (the same groups where both
+ * workspaces hold them, behind the minimum here too).  micro_batch <= 0 picks a default: the largest micro-batch whose
  * input and output activations fit 128 MiB (the whole batch whenever the
  * stage's activations already fit the Infinity Cache); a micro_batch >= N
  * runs the whole batch per block.  ws needs cf_stage_microbatch_workspace_bytes() bytes: two

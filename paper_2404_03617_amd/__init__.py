@@ -253,6 +253,34 @@ def _workspace(x: torch.Tensor, ws, need: int):
     return ws
 
 
+# The hidden-layer split of wide blocks over few pixels keeps fp32 partials in
+# scratch memory.  Above SPLIT_PIXELS there are tiles enough for every CU,
+# beyond SPLIT_HIDDEN channels the kernel's LDS has no room, and SPLIT_BYTES is
+# what the library uses at most.
+SPLIT_PIXELS, SPLIT_HIDDEN, SPLIT_BYTES = 4096, 3584, 16 << 20
+
+
+def _split_bytes(x: torch.Tensor, hidden: int) -> int:
+    """Scratch worth adding to a stage's workspace for the hidden split (0:
+    the shape has none)."""
+    N, H, W, C = x.shape
+    pixels = N * H * W
+    if pixels > SPLIT_PIXELS or C < 256 or hidden > SPLIT_HIDDEN:
+        return 0
+    return min(SPLIT_BYTES, 64 * pixels * C * 4)
+
+
+def _scratch(x: torch.Tensor, nbytes: int, stream):
+    """`nbytes` of device memory for one call (None for 0), safe to drop while
+    the call still runs on `stream`."""
+    if not nbytes:
+        return None
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=x.device)
+    if stream is not None:
+        ws.record_stream(stream)
+    return ws
+
+
 def _prepare_block(x: torch.Tensor, p: dict, act: str, out):
     """Every check of a block call, in an order that needs no GPU: shapes and
     dtypes first, then devices.  Returns (y, struct, keep, dims)."""
@@ -267,8 +295,14 @@ def _prepare_block(x: torch.Tensor, p: dict, act: str, out):
 
 def block_forward(x: torch.Tensor, p: dict, act: str = "gelu", out: torch.Tensor | None = None,
                   stream=None) -> torch.Tensor:
-    """Fused ConvFirst block (one kernel launch): y = x + FFN(dwconv(x))."""
+    """Fused ConvFirst block: y = x + FFN(dwconv(x)).  A wide block over few
+    pixels takes scratch memory for its hidden split from torch's allocator."""
     y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out)
+    ws = _scratch(x, _split_bytes(x, E * C), stream)
+    if ws is not None:  # the hidden split beats every configuration the tuner knows
+        _check(lib().cf_stage_forward(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), ctypes.byref(bp), 1, N, H, W, C, E, k,
+                                      DTYPES[x.dtype], ACTS[act], _stream(stream)))
+        return y
     _check(lib().cf_block_forward(_ptr(x), _ptr(y), ctypes.byref(bp), N, H, W, C, E, k,
                                   DTYPES[x.dtype], ACTS[act], _stream(stream)))
     return y
@@ -277,10 +311,13 @@ def block_forward(x: torch.Tensor, p: dict, act: str = "gelu", out: torch.Tensor
 def block_autotune(x: torch.Tensor, p: dict, act: str = "gelu", out: torch.Tensor | None = None,
                    stream=None) -> torch.Tensor:
     """Time every kernel configuration that applies to this block shape, cache
-    the fastest for later block_forward calls, return the block's output."""
+    the fastest for later block_forward calls (those with a hidden split keep
+    it), return the block's output."""
     y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out)
     _check(lib().cf_block_autotune(_ptr(x), _ptr(y), ctypes.byref(bp), N, H, W, C, E, k,
                                    DTYPES[x.dtype], ACTS[act], _stream(stream)))
+    if _split_bytes(x, E * C):
+        return block_forward(x, p, act, out=y, stream=stream)
     return y
 
 
@@ -307,7 +344,7 @@ def stage_forward(x: torch.Tensor, blocks: list, act: str = "gelu", out=None, ws
     y = _out(x, out)
     L = lib()
     need = L.cf_stage_workspace_bytes(len(blocks), N, H, W, C, DTYPES[x.dtype])
-    ws = _workspace(x, ws, need)
+    ws = _scratch(x, need + _split_bytes(x, E * C), stream) if ws is None else _workspace(x, ws, need)
     arr = (_BlockParams * len(blocks))(*structs)
     _check(L.cf_stage_forward(_ptr(x), _ptr(y), _ptr(ws), 0 if ws is None else ws.numel(),
                               arr, len(blocks), N, H, W, C, E, k, DTYPES[x.dtype], ACTS[act],
@@ -334,7 +371,7 @@ def stage_forward_microbatch(x: torch.Tensor, blocks: list, act: str = "gelu", m
     y = _out(x, out)
     L = lib()
     need = L.cf_stage_microbatch_workspace_bytes(len(blocks), N, H, W, C, micro_batch, DTYPES[x.dtype])
-    ws = _workspace(x, ws, need)
+    ws = _scratch(x, need + _split_bytes(x, E * C), stream) if ws is None else _workspace(x, ws, need)
     arr = (_BlockParams * len(blocks))(*structs)
     _check(L.cf_stage_forward_microbatch(_ptr(x), _ptr(y), _ptr(ws), 0 if ws is None else ws.numel(), arr,
                                          len(blocks), N, H, W, C, E, k, micro_batch, DTYPES[x.dtype], ACTS[act],
@@ -639,10 +676,7 @@ def mbconv_forward(x: torch.Tensor, p: dict, out=None, ws=None, launch: str = "c
     (N, H, W, C, E, R, _, k), mp, keep = _mbconv_args(x, p, launch, False)
     y = _out(x, out)
     if ws is None:
-        ws = torch.empty(max(1, mbconv_workspace_bytes(N, H, W, C, E, R, x.dtype)), dtype=torch.uint8,
-                         device=x.device)
-        if stream is not None:
-            ws.record_stream(stream)  # freed here, in use there
+        ws = _scratch(x, max(1, mbconv_workspace_bytes(N, H, W, C, E, R, x.dtype)), stream)
     else:
         _workspace(x, ws, 0)
     _check(lib().cf_mbconv_forward(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), ctypes.byref(mp), N, H, W, C, E,
@@ -662,10 +696,7 @@ def mbconv_s2_forward(x: torch.Tensor, p: dict, out=None, ws=None, launch: str =
     (N, H, W, C, E, R, K, k), mp, keep = _mbconv_args(x, p, launch, True)
     y = _out(x, out, (N, (H + 1) // 2, (W + 1) // 2, K))
     if ws is None:
-        ws = torch.empty(max(1, mbconv_s2_workspace_bytes(N, H, W, C, E, R, K, x.dtype)), dtype=torch.uint8,
-                         device=x.device)
-        if stream is not None:
-            ws.record_stream(stream)  # freed here, in use there
+        ws = _scratch(x, max(1, mbconv_s2_workspace_bytes(N, H, W, C, E, R, K, x.dtype)), stream)
     else:
         _workspace(x, ws, 0)
     _check(lib().cf_mbconv_s2_forward(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), ctypes.byref(mp), N, H, W, C, E,

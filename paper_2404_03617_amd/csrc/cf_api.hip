@@ -371,27 +371,28 @@ size_t stage_ws_min(int depth, int N, int H, int W, int C, cf_dtype dt) {
     return round256((size_t)N * H * W * C * elem_bytes(dt));
 }
 
-// Hidden-layer groups a C = 512 fp16 stage uses when the workspace allows it:
-// enough (tile, group) pairs to fill the chip, at most STAGE_GROUPS.
+// fp32 partials that the recommended workspace of a C = 512 fp16 stage holds
 constexpr int STAGE_GROUPS = 4;
-int stage_groups(int N, int H, int W, int C, int E, cf_dtype dt) {
-    if (C != 512 || dt != CF_F16)
-        return 1;
-    const int64_t tiles = ((int64_t)N * H * W + 127) / 128;
-    const int chunks = E * C / 32;
-    const int cus = cf::device_cu_count();
-    int g = 1;
-    while (g * 2 <= STAGE_GROUPS && chunks % (g * 2) == 0 && tiles * g * 2 <= cus + cus / 4)
-        g *= 2;
-    return g;
+// ... and up to 8 at C = 256, where few pixels leave most CUs without a tile
+constexpr size_t SPLIT_PIXELS = 4096, SPLIT_BYTES = (size_t)16 << 20;
+
+// Hidden-layer groups for a batch `whole`, of which `part` runs per launch,
+// with `bytes` of room for the partials.
+static int fit_groups(const cf::Shape &whole, size_t bytes, const cf::Shape &part) {
+    const int g = cf::ffn_groups(whole);
+    const size_t one = (size_t)part.N * part.H * part.W * part.C * sizeof(float);
+    return (size_t)g * one <= bytes ? g : (int)(bytes / one);
 }
 
 size_t cf_stage_workspace_bytes(int depth, int N, int H, int W, int C, cf_dtype dt) {
     if (N <= 0 || H <= 0 || W <= 0 || C <= 0)
         return 0;
     size_t b = stage_ws_min(depth, N, H, W, C, dt);
+    const size_t one = (size_t)N * H * W * C * sizeof(float);
     if (C == 512 && dt == CF_F16)
-        b += (size_t)STAGE_GROUPS * N * H * W * C * sizeof(float);
+        b += STAGE_GROUPS * one;
+    else if (C == 256 && (size_t)N * H * W <= SPLIT_PIXELS)
+        b += (SPLIT_BYTES / one < 8 ? SPLIT_BYTES / one : 8) * one;
     return b;
 }
 
@@ -439,23 +440,25 @@ cf_status cf_stage_forward(const void *x, void *y, void *ws, size_t ws_bytes, co
         g_err[0] = 0;
         return CF_OK;
     }
-    // hidden-layer split with fp32 partials after the ping-pong buffer, when
-    // the workspace holds them
+    // few pixels: the hidden layer split into groups, their fp32 partials
+    // after the ping-pong buffer as far as the workspace holds them
     int groups = 1;
     float *partial = nullptr;
-    // (a handful of pixels: the slice kernel, which needs no partials)
-    const int g = cf::slice_applies(s) ? 1 : stage_groups(N, H, W, C, E, dt);
-    const size_t pbytes = (size_t)g * N * H * W * C * sizeof(float);
-    if (g > 1 && ws && aligned16(ws) && ws_bytes >= need + pbytes &&
-        !overlap((char *)ws + need, pbytes, x, bytes) && !overlap((char *)ws + need, pbytes, y, bytes)) {
-        groups = g;
-        partial = (float *)((char *)ws + need);
+    cf::Shape sb = s;
+    if (ws && aligned16(ws) && ws_bytes > need) {
+        const int g = fit_groups(s, ws_bytes - need, s);
+        const size_t pbytes = (size_t)g * N * H * W * C * sizeof(float);
+        if (g > 1 && !overlap((char *)ws + need, pbytes, x, bytes) && !overlap((char *)ws + need, pbytes, y, bytes)) {
+            groups = g;
+            partial = (float *)((char *)ws + need);
+            sb.cfg = cf::CFG_FFN;
+        }
     }
     // block i writes y when (depth-1-i) is even, else ws, so the last one lands in y
     const void *in = x;
     for (int i = 0; i < depth; i++) {
         void *out = ((depth - 1 - i) % 2 == 0) ? y : ws;
-        hipError_t e = cf::launch_fused_block(in, out, to_w(&blocks[i]), s, groups, partial, (hipStream_t)stream);
+        hipError_t e = cf::launch_fused_block(in, out, to_w(&blocks[i]), sb, groups, partial, (hipStream_t)stream);
         if (e != hipSuccess)
             return hip_fail(e, "cf_stage_forward");
         in = out;
@@ -524,17 +527,33 @@ cf_status cf_stage_forward_microbatch(const void *x, void *y, void *ws, size_t w
     // enough for the slice kernel (whose expand sums in another order) runs
     // the tile kernels of the whole batch when that batch is not itself a
     // slice shape
-    const bool full_slice = cf::slice_applies(to_shape(N, H, W, C, E, k, dt, act));
+    const cf::Shape whole = to_shape(N, H, W, C, E, k, dt, act);
+    const bool full_slice = cf::slice_applies(whole);
+    // the plain stage's hidden groups, where the workspace has room for them
+    int groups = 1;
+    float *partial = nullptr;
+    if (ws && aligned16(ws) && ws_bytes > need) {
+        const int g = fit_groups(whole, ws_bytes - need, to_shape(m, H, W, C, E, k, dt, act));
+        const size_t pbytes = (size_t)g * m * H * W * C * sizeof(float);
+        if (g > 1 && !overlap((char *)ws + need, pbytes, x, bytes) && !overlap((char *)ws + need, pbytes, y, bytes)) {
+            groups = g;
+            partial = (float *)((char *)ws + need);
+        }
+    }
     for (int n0 = 0; n0 < N; n0 += m) {
         const int mb = N - n0 < m ? N - n0 : m;
         cf::Shape s = to_shape(mb, H, W, C, E, k, dt, act);
         s.cfg = tuned_config(s);
         if (s.cfg == cf::CFG_DEFAULT && !full_slice && cf::slice_applies(s) && cf::tile_fits(s))
             s.cfg = cf::CFG_TILE;
+        if (s.cfg != cf::CFG_GENERIC && !cf::ffn_applies(whole) && cf::ffn_applies(s))
+            s.cfg = cf::CFG_SINGLE;
+        if (groups > 1)
+            s.cfg = cf::CFG_FFN;
         const void *in = (const char *)x + (size_t)n0 * img;
         for (int i = 0; i < depth; i++) {
             void *out = (i == depth - 1) ? (void *)((char *)y + (size_t)n0 * img) : (void *)buf[i & 1];
-            hipError_t e = cf::launch_fused_block(in, out, to_w(&blocks[i]), s, 1, nullptr, (hipStream_t)stream);
+            hipError_t e = cf::launch_fused_block(in, out, to_w(&blocks[i]), s, groups, partial, (hipStream_t)stream);
             if (e != hipSuccess)
                 return hip_fail(e, what);
             in = out;

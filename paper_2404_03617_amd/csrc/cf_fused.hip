@@ -9,10 +9,12 @@
 // device memory.
 //
 //   C = 64, fp16        cf_block64.h  all weights resident in LDS, 64-pixel waves
-//   C = 128/256, fp16   cf_wide.h     wave pairs per block, DMA-fed weight buffers
-//   C = 512, fp16       cf_wide.h     one wave per block, chunk ring, optional
-//                                     hidden groups (fp32 partials + reduction)
-//   bf16, other shapes  cf_fused_impl.h
+//   C = 128, fp16       cf_wide.h     wave pairs per block, DMA-fed weight buffers
+//   C = 128 bf16,       cf_ffn.h      two launches: depth-wise into y, then the
+//   C = 256, 512                      FFN in place; optional hidden groups
+//   C = 64 bf16, others cf_fused_impl.h
+// (E above what cf_ffn.h holds: cf_wide.h for fp16, cf_fused_impl.h and
+// cf_small.hip for bf16.)
 //
 // Hidden-split mode (groups > 1): workgroup (tile, g) runs only its range of
 // chunks and writes an fp32 partial of the projected output; split_reduce_kernel
@@ -110,7 +112,11 @@ hipError_t launch_fused_block(const void *x, void *y, const BlockW &w, const Sha
     a.P = (uint32_t)((int64_t)s.N * s.H * s.W);
     hipError_t e;
     bool done = false;
-    if (groups > 1) {
+    if (groups > 1 && s.cfg == CFG_FFN) {
+        if ((e = launch_ffn_block(x, y, w, s, groups, partial, st)) != hipSuccess)
+            return e;
+        done = true;
+    } else if (groups > 1) {
         e = launch_small_split(x, w, s, groups, partial, st);
         if (e != hipErrorInvalidConfiguration) {
             if (e != hipSuccess)
@@ -119,9 +125,13 @@ hipError_t launch_fused_block(const void *x, void *y, const BlockW &w, const Sha
         }
     }
     // a handful of pixels: the slice kernel (no workspace) unless the
-    // autotuner chose the tile kernels (CFG_TILE) or the generic one
+    // autotuner chose the kernels of larger shapes (CFG_TILE) or the generic one
     if (!done && groups <= 1 && s.cfg == CFG_DEFAULT && slice_applies(s))
         return launch_slice(x, y, w, s, st);
+    // wide blocks: depth-wise into y, then the FFN in place (CFG_TILE: the
+    // same for a slice-sized part of a larger batch)
+    if (!done && groups <= 1 && s.cfg != CFG_GENERIC && s.cfg != CFG_SINGLE && ffn_applies(s))
+        return launch_ffn_block(x, y, w, s, 1, nullptr, st);
     const bool special = s.cfg != CFG_GENERIC;
     // C = 512 in bf16 has no streaming kernel of its own: the single-group
     // small kernel (one workgroup per 128-pixel tile and 128 output channels,

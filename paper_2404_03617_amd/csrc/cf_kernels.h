@@ -54,7 +54,9 @@ enum {
     CFG_GENERIC = 1,     // the generic fused kernel (cf_fused_impl.h)
     CFG_HALF_TILE = 2,   // C = 64 fp16 kernel with tiles of at most half the blocks
     CFG_TILE = 3,        // N*H*W <= 64: the tile kernels where the default is the slice kernel
-    CFG_COUNT = 4
+    CFG_COUNT = 4,
+    CFG_FFN = 8,         // the two-launch block split into hidden groups (never autotuned: needs a workspace)
+    CFG_SINGLE = 9       // the single-launch kernel, for a part of a batch that takes it as a whole
 };
 // Whether configuration cfg applies to shape s.
 bool cfg_applies(const Shape &s, int cfg);
@@ -84,6 +86,14 @@ hipError_t launch_convfirst_s2(const void *x, void *y, const BlockW &w, int N, i
                                int bf16, int act, hipStream_t st);
 bool slice_applies(const Shape &s);
 hipError_t launch_slice(const void *x, void *y, const BlockW &w, const Shape &s, hipStream_t st);
+
+// Wide blocks as a depth-wise launch into y and the FFN in place (cf_ffn.h).
+// groups > 1: partial holds fp32 [groups][N*H*W][C]; the caller adds the
+// groups, b2 and x.  ffn_groups: how many a shape is worth, 1 for none.
+bool ffn_applies(const Shape &s);
+int ffn_groups(const Shape &s);
+hipError_t launch_ffn_block(const void *x, void *y, const BlockW &w, const Shape &s, int groups, float *partial,
+                            hipStream_t st);
 
 // LDS bytes of the small-batch kernel for this shape; 0 when it does not apply.
 // direct: one hidden group writing y (no tile-count limit); otherwise the

@@ -289,3 +289,63 @@ def test_workload_stack():
     ref = oracle.stack_forward(synth.to_f64(x), [(kd, synth.params_f64(p)) for kd, p in layers])
     r = assert_close(y.cpu(), ref, what=name)
     say("  stack rel err %.2e" % r)
+
+
+# The two-launch wide blocks (depth-wise into y, FFN in place): every pixel
+# tile of C = 256 (P up to 8192, 16384, above) and its remainders, an odd
+# number of 64-channel chunks, both depth-wise kernels (strips of 7 and 4
+# pixels with overhang, one pixel per thread), C = 128 and 512 with a ragged
+# last tile, and the hidden groups with an uneven last group.
+WIDE = [
+    # C, E, k, N, H, W
+    (256, 3, 3, 1, 3, 7), (256, 4, 5, 2, 9, 9), (256, 1, 7, 3, 13, 11), (256, 2, 3, 47, 14, 13),
+    (256, 3, 1, 50, 14, 13), (256, 2, 3, 93, 14, 13), (128, 3, 3, 3, 27, 35), (128, 2, 7, 2, 5, 9),
+    (512, 3, 3, 2, 7, 5), (512, 4, 3, 3, 8, 7),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("case", WIDE, ids=lambda c: "C%d_E%d_k%d_N%d_%dx%d" % c)
+def test_wide_two_launch_blocks_match_oracle(case, dtype):
+    C, E, k, N, H, W = case
+    say("wide two-launch", case, dtype)
+    x, p = make_block(61, N, H, W, C, E, k, dtype)
+    pick = sorted({0, N // 2, N - 1})
+    ref = oracle_block(x[pick], p)
+    diag = DIAG_F16 if dtype == "f16" else None
+    xd, pd = x.cuda(), to_dev(p)
+    y = cf.block_forward(xd, pd)
+    torch.cuda.synchronize()
+    assert_close(y.cpu()[pick], ref, what="wide %s %s" % (case, dtype), diag=diag)
+    # without room for hidden groups, and with room for three of them
+    P = N * H * W
+    for groups in (0, 3):
+        ws = torch.empty(groups * P * C * 4 + 256, dtype=torch.uint8, device="cuda")
+        y1 = cf.stage_forward(xd, [pd], ws=ws) if cf.lib().cf_stage_workspace_bytes(
+            1, N, H, W, C, cf.DTYPES[x.dtype]) <= ws.numel() else None
+        torch.cuda.synchronize()
+        if y1 is not None:
+            assert_close(y1.cpu()[pick], ref, what="wide %s %s groups %d" % (case, dtype, groups), diag=diag)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_wide_blocks_depend_on_neither_tile_nor_batch(dtype):
+    """One image alone and inside batches that take every pixel tile: the same
+    bits (the order of the sums depends on neither).  Through the C entry
+    point, which has no room for hidden groups."""
+    import ctypes
+    x, p = make_block(63, 100, 14, 13, 256, 2, 5, dtype)
+    xd, pd = x.cuda(), to_dev(p)
+    keep = []
+    bp = cf._block_struct(xd, pd, keep)
+
+    def run(n):
+        y = torch.empty_like(xd[:n])
+        cf._check(cf.lib().cf_block_forward(xd.data_ptr(), y.data_ptr(), ctypes.byref(bp), n, 14, 13, 256, 2, 5,
+                                            cf.DTYPES[xd.dtype], 0, None))
+        torch.cuda.synchronize()
+        return y
+
+    whole = run(100)
+    for n in (1, 40, 60):
+        assert torch.equal(run(n), whole[:n])

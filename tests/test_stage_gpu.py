@@ -41,6 +41,8 @@ def oracle_stage(x, blocks, act="gelu"):
     (4, 6, 6, 10, 64, 4, 3, 1, "bf16"),    # one image at a time
     (1, 5, 8, 8, 128, 4, 3, 2, "f16"),     # a single block needs no workspace
     (2, 3, 5, 5, 64, 4, 3, 8, "f16"),      # micro-batch larger than the batch
+    (2, 93, 14, 13, 256, 1, 3, 40, "f16"),  # parts small enough for two launches a block, the whole batch not
+    (2, 9, 9, 7, 256, 2, 3, 4, "bf16"),    # hidden groups, of the whole batch's number
 ], ids=lambda c: "D%d_N%d_%dx%d_C%d_E%d_k%d_m%d_%s" % c)
 def test_microbatch_stage_matches_oracle_and_plain_stage(case):
     depth, N, H, W, C, E, k, m, dtype = case
