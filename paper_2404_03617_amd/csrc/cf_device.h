@@ -104,8 +104,25 @@ __device__ __forceinline__ half2v gelu_pk_f16_quarter(half2v w) {
     return w * p;
 }
 
-// Exact-erf GELU in fp32 (bf16 path; the device erff of the ROCm math library).
-__device__ __forceinline__ float gelu_f32(float u) { return 0.5f * u * (1.0f + erff(u * 0.70710678118654752f)); }
+// GELU in fp32 for the bf16 kernels and those that keep the hidden layer in
+// fp32: with erfc from Abramowitz & Stegun 7.1.26 (|error| <= 1.5e-7),
+//   GELU(u) = max(u, 0) - |u| / 2 erfc(|u| / sqrt 2),
+//   erfc(x) ~= (a1 t + .. + a5 t^5) exp(-x^2),  t = 1 / (1 + p x),
+// which has no cancellation for u < 0, and p / sqrt 2, log2 e / 2 and the
+// halves folded into the constants: eleven instructions, a reciprocal and an
+// exponential, no branch (the library erff takes two divergent paths of about
+// thirty).  |error| < 3e-7 max(1, |u|).  |u| is capped where the product is 0
+// anyway, so that infinities stay infinities.
+__device__ __forceinline__ float gelu_f32(float u) {
+    const float t = __builtin_amdgcn_rcpf(fmaf(fabsf(u), 0.231641888f, 1.0f));
+    float q = fmaf(0.530702715f, t, -0.726576014f);
+    q = fmaf(q, t, 0.710706871f);
+    q = fmaf(q, t, -0.142248368f);
+    q = fmaf(q, t, 0.127414796f);
+    q *= t;
+    q *= __builtin_amdgcn_exp2f(u * u * -0.721347520f);
+    return fmaf(-fminf(fabsf(u), 32.0f), q, fmaxf(u, 0.0f));
+}
 
 enum { ACT_GELU = 0, ACT_RELU = 1, ACT_NONE = 2 };
 

@@ -64,22 +64,6 @@ constexpr uint32_t slot_bytes(int C) { return (uint32_t)(C / 8 * shares(C)) * PI
 // LDS: two chunk slots, then s1 and b1 of the group's channels (fp16: a quarter of each)
 constexpr uint32_t lds_bytes(int C, int channels) { return 2 * slot_bytes(C) + 8 * (uint32_t)channels; }
 
-// GELU in fp32 with erf from Abramowitz & Stegun 7.1.26 (|error| <= 1.5e-7):
-// a reciprocal, an exponential and no branch
-__device__ __forceinline__ float gelu_as(float u) {
-    const float x = fabsf(u) * 0.70710678118654752f;
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, x, 1.0f));
-    float q = fmaf(1.061405429f, t, -1.453152027f);
-    q = fmaf(q, t, 1.421413741f);
-    q = fmaf(q, t, -0.284496736f);
-    q = fmaf(q, t, 0.254829592f);
-    q *= t;
-    const float e = __builtin_amdgcn_exp2f(x * x * -1.4426950408889634f);  // exp(-x^2)
-    const float erf_x = fmaf(-q, e, 1.0f);
-    const float hu = 0.5f * u;
-    return fmaf(hu, copysignf(erf_x, u), hu);
-}
-
 __device__ __forceinline__ void dma16s_at(const void *base, uint32_t voff, uint32_t lds_addr) {
     const uint32_t lds = (uint32_t)__builtin_amdgcn_readfirstlane(lds_addr);
     const uint64_t b = (uint64_t)(uintptr_t)base;
@@ -259,8 +243,8 @@ __global__ __launch_bounds__(PG * shares(C) * 64) __attribute__((amdgpu_waves_pe
                     uint32_t v;
                     if constexpr (T::is_bf16) {
                         if constexpr (ACT == ACT_GELU) {
-                            u0 = gelu_as(u0);
-                            u1 = gelu_as(u1);
+                            u0 = gelu_f32(u0);
+                            u1 = gelu_f32(u1);
                         } else if constexpr (ACT == ACT_RELU) {
                             u0 = fmaxf(u0, 0.0f);
                             u1 = fmaxf(u1, 0.0f);
