@@ -5,64 +5,55 @@
 // of the block input, the two maps concatenated (2C channels, conv output
 // first) into the expand, activation, project to K, no residual.
 //
-// Work unit: 16 output pixels of one output row (columns j0 .. j0 + 15).
-// The waves are persistent: each takes units blockIdx * nw + wave, then
-// every gridDim * nw-th, in a private LDS region; the taps, s0, b0, s1, b1,
-// s2 and b2 are staged in LDS once per workgroup.  Per unit:
-//  1. the input window, rows 2i - 2 .. 2i + 2 and columns 2j0 - 2 .. 2j0 + 32,
-//     zero outside the image (the conv's padding): every lane's pieces are
-//     loaded with one batch of 16-byte loads (addresses clamped into the
-//     image, the zeros selected at the LDS store); with up to 32 channels
-//     the next unit's window is loaded during this unit's conv and FFN;
-//  2. the grouped conv at full resolution, rows 2i - 1 .. 2i + 1 and columns
-//     2j0 - 1 .. 2j0 + 31 (the positions the blur reads, before reflection),
-//     on v_mfma_f32_16x16x32: for group g and tap column dj, A row m = 8s + o
-//     at K index 8R + t is the tap W[R - s][dj][8g + o][t] (zero unless
-//     0 <= R - s <= 2) and B column j at K index 8R + t is window pixel
-//     (w0 + R, c + j + dj), channel 8g + t, so one product per tap column
-//     gives conv rows w0 and w0 + 1 of 16 columns; two row sets (w0 = 0, and
-//     w0 = 1 keeping only its second row) and three column tiles (the third
-//     for column 2j0 + 31 alone) cover the 3 x 33 positions.  The A
-//     fragments of a group (one per tap column) stay in registers for all
-//     its products; s0, b0; rounded to the I/O dtype;
+// A workgroup of eight waves takes tiles of TR output rows x 16 columns, one
+// after the other; the taps, s0, b0, s1, b1, s2 and b2 are staged in LDS once
+// per workgroup, and W1 and W2 as well when they fit.  Per tile, with a
+// barrier between the steps:
+//  1. the input window, rows 2i0 - 2 .. 2i0 + 2TR and columns 2j0 - 2 ..
+//     2j0 + 32, zero outside the image (the conv's padding), from registers
+//     to LDS; the next tile's window is then loaded into the same registers
+//     (addresses clamped, the zeros selected at the LDS store);
+//  2. the grouped conv at full resolution, rows 2i0 - 1 .. 2i0 + 2TR - 1 and
+//     columns 2j0 - 1 .. 2j0 + 31 (the positions the blur reads, before
+//     reflection), on v_mfma_f32_16x16x32: for group g and tap column dj, A
+//     row m = 8s + o at K index 8R + t is the tap W[R - s][dj][8g + o][t]
+//     (zero unless 0 <= R - s <= 2) and B column j at K index 8R + t is
+//     window pixel (w0 + R, c + dj), channel 8g + t, so one product per tap
+//     column gives conv rows w0 and w0 + 1 of 16 positions; the positions of
+//     a row pair follow those of the last in one sequence of 33 per pair; s0,
+//     b0; rounded to the I/O dtype;
 //  3. the blur of both maps (fp32, rounded to the I/O dtype), each read at
-//     the reflected positions, into a 16-pixel tile of 2C channels,
+//     the reflected positions, into a tile of 16 TR pixels x 2C channels,
 //     zero-padded to a multiple of 32;
-//  4. the FFN on v_mfma_f32_16x16x32 in chunks of 32 hidden channels:
-//     expand tiles of 16 hidden channels (A = W1 rows, B = the tile), s1, b1
-//     and the activation in fp32, rounded; two tiles form the B operand of
-//     the project with the K order position 8q + e <-> hidden 32kk + 4q + e
-//     (e < 4) or 32kk + 16 + 4q + e - 4, the lane layout the expand leaves,
-//     and the W2 fragments are read in that order; s2, b2; y stored once.
-//     When W1 and W2 fit in LDS beside the regions with two waves per
-//     SIMD (or as many as without them), the workgroup stages them there
-//     once (rows padded by 16 bytes, so the sixteen rows of a fragment read
-//     fall in distinct banks) and the fragments are read from LDS.  Otherwise a chunk's W1 and W2
-//     pieces are loaded from global memory (L2) one chunk ahead, the first
-//     chunk's during the conv.  Every load of the loop is unconditional (addresses clamped; the
-//     rows past R meet zero hidden values, the rows past K are not stored),
-//     so the waits count exactly.  The loads are row-major -- lane 4r + p
-//     takes piece p of row r, four adjacent lanes on one contiguous run --
-//     and ds_bpermute from lane 4 jl + q moves each dword to the fragment
-//     lane (jl, q) when the chunk is used (a fragment-order load, sixteen
-//     rows in sixteen adjacent lanes, costs the memory unit several times
-//     more per byte).
-// The input windows of neighbouring units overlap by three columns and the
-// conv positions on the unit's border columns are evaluated by both units.
+//  4. the expand on v_mfma_f32_16x16x32: a wave takes tiles of 16 hidden
+//     channels over every pixel of the tile (A = W1 rows), s1, b1 and the
+//     activation in fp32, rounded into LDS over the dead window and conv map;
+//  5. the project: the products of 16 output channels (A = W2 rows) and 16
+//     pixels dealt evenly to the waves; s2, b2; y stored once.
+// Weights that are not in LDS are read from global memory (L2) one tile ahead
+// with row-major loads -- lane 4r + p takes piece p of row r, four adjacent
+// lanes on one contiguous run -- and ds_bpermute moves each dword to its
+// fragment lane (a fragment-order load costs the memory unit several times
+// more per byte).
 // Conv positions outside the image are evaluated on the zero padding and
 // never read: the blur's reflection of row -1 is row 1, of row H is H - 2,
-// both inside the unit's rows (and likewise for columns).
+// both inside the tile's rows (and likewise for columns).
+//
+// Bound by the chain of the five steps at eight or sixteen waves per CU.  A wave working
+// alone on units of 16 pixels (the earlier form of this kernel) left room for
+// four waves in the LDS at C = 48 and read every weight from L2 for each unit:
+// N = 128, 64 x 64, C = 48, R = 288, K = 64, fp16: 151 us then, 89 us now.
 #include "cf_device.h"
 #include "cf_kernels.h"
 
 namespace cf {
 namespace cfs2 {
 
-constexpr int XR = 5, XC = 35;  // input window: rows 2i-2 .. 2i+2, columns 2j0-2 .. 2j0+32
-constexpr int VR = 3, VC = 33;  // conv outputs: rows 2i-1 .. 2i+1, columns 2j0-1 .. 2j0+31
-constexpr int UPX = 16;         // output pixels per unit
+constexpr int XC = 35;          // window columns 2j0-2 .. 2j0+32
+constexpr int VC = 33;          // conv columns 2j0-1 .. 2j0+31
 constexpr int KMAX = 128;       // output channels
 constexpr int RMAX = 1024;      // hidden channels
+constexpr int NW = 8, NT = NW * 64;
 
 struct Args {
     const uint16_t *x;
@@ -74,20 +65,16 @@ struct Args {
     const uint16_t *w2;  // [K][R]
     const float *s2, *b2;
     int H, W, Ho, Wo, R, K, act;
-    int units, jt;        // units = N * Ho * jt, jt = ceil(Wo / 16)
-    int nw;               // waves per workgroup
+    int tiles;                // N * it * jt
+    FastDiv jt, it;           // tiles per row of tiles, rows of tiles per image
     uint32_t off_w1, off_w2;  // LDS: taps, s0, b0, s1, b1, s2, b2; W1 and W2 when staged;
-    uint32_t off_region;      // then one region per wave
+    uint32_t off_x, off_z;    // then window and conv map (later the hidden tile); then the blurred tile
 };
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// v_mul_u32_u24 (both factors below 2^24)
-__device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b) { return (uint32_t)__umul24(a, b); }
-
-// one pixel of reflect padding (-1 -> 1, n -> n - 2); past that (the padded
-// pixels of a unit at the right edge, whose outputs are not stored) the last
-// column
+// one pixel of reflect padding (-1 -> 1, n -> n - 2); past that (positions of
+// a ragged tile whose outputs are not stored) the last one
 __device__ __forceinline__ int refl(int v, int n) {
     int r = v < 0 ? -v : v;
     r = r == n ? n - 2 : r;
@@ -98,458 +85,425 @@ __device__ __forceinline__ float act_f(float u, int act) {
     if (act == ACT_RELU)
         return fmaxf(u, 0.0f);
     if (act == ACT_GELU)
-        return 0.5f * u * (1.0f + erff(u * 0.70710678118654752f));
+        return gelu_f32(u);
     return u;
 }
+
+__device__ __forceinline__ u32x4 ld16(const void *p) { return *reinterpret_cast<const u32x4 *>(p); }
 
 // LDS bytes of the staged taps and vectors
 __host__ __device__ inline uint32_t staged_bytes(int C, int R, int K) {
     return ((uint32_t)(9 * C * 16 + 4 * (2 * C + 2 * R + 2 * K)) + 255) & ~255u;
 }
 
-// row strides of W1 and W2 staged in LDS
+// row strides of W1 and W2 staged in LDS, and of the hidden tile: odd
+// multiples of 16 bytes
 __host__ __device__ inline uint32_t w1_stride(int C) { return (uint32_t)(4 * C + 16); }
 __host__ __device__ inline uint32_t w2_stride(int R) { return (uint32_t)(2 * R + 16); }
 __host__ __device__ inline uint32_t weights_bytes(int C, int R, int K) {
     return ((uint32_t)R * w1_stride(C) + (uint32_t)K * w2_stride(R) + 255) & ~255u;
 }
 
-template <typename T, int C, int OTM, bool WL>
+// bytes per window / conv pixel: an odd multiple of 16
+constexpr uint32_t pixel_bytes(int C) { return C % 16 ? 2 * C + 32 : 2 * C + 16; }
+constexpr int row_pairs(int TR) { return TR + 1; }  // of the 2 TR + 1 conv rows
+
+// LDS bytes of the window and conv map, or the hidden tile over them
+inline uint32_t map_bytes(int C, int TR, int R) {
+    const uint32_t xv = ((uint32_t)(2 * TR + 3) * XC + (uint32_t)(2 * TR + 1) * VC) * pixel_bytes(C);
+    const uint32_t h = (uint32_t)(16 * TR) * w2_stride(R);
+    return ((xv > h ? xv : h) + 255) & ~255u;
+}
+inline uint32_t tile_bytes(int C, int TR) { return (uint32_t)(16 * TR) * (2 * (uint32_t)((2 * C + 31) / 32 * 32) + 16); }
+
+template <typename T, int C, int TR, bool WL>
 struct Kern {
-    static constexpr int G = C / 8;                            // groups of the conv
-    static constexpr uint32_t PP = 2 * C + 16;                 // LDS bytes per window / conv pixel
+    static constexpr int G = C / 8;                      // groups of the conv
+    static constexpr uint32_t PP = pixel_bytes(C);
     static constexpr int C2 = 2 * C, C2P = (C2 + 31) / 32 * 32;
-    static constexpr int KS = C2P / 32;                        // expand K steps
-    static constexpr uint32_t PZ = 2 * C2P + 16;               // LDS bytes per tile pixel
-    static constexpr uint32_t XB = XR * XC * PP, VB = VR * VC * PP, ZB = UPX * PZ;
-    static constexpr uint32_t REGION = XB + VB + ZB;
-    static constexpr int NX = XR * XC * G;                     // 16-byte pieces of a window
-    static constexpr int NIT = (NX + 63) / 64;                 // per lane
-    static constexpr bool PREF = G <= 4;                       // next window loaded during this unit
+    static constexpr int KS = C2P / 32;                  // expand K steps
+    static constexpr uint32_t PZ = 2 * C2P + 16;         // LDS bytes per tile pixel
+    static constexpr int RP = row_pairs(TR);
+    static constexpr int XR = 2 * TR + 3;                // window rows
+    static constexpr int VR = 2 * TR + 1;
+    static constexpr uint32_t XB = (uint32_t)XR * XC * PP;
+    static constexpr int NX = XR * XC * G, NIT = (NX + NT - 1) / NT;  // 16-byte pieces of the window, per thread
+    static constexpr int NPOS = RP * VC, PT = (NPOS + 15) / 16;       // conv positions per group, tiles of 16
 
-    struct Frag {
-        u32x4 w1[2][KS];
-        u32x2 w2[OTM][2];
+    struct Tile {
+        int n, i0, j0;
     };
-
-    struct Unit {
-        int n, i, j0;
-    };
-
-    static __device__ __forceinline__ Unit decode(const Args &a, int u) {
-        const int jt = u % a.jt, ni = u / a.jt;
-        return Unit{ni / a.Ho, ni % a.Ho, jt * UPX};
+    static __device__ __forceinline__ Tile decode(const Args &a, int u) {
+        const uint32_t r = fdiv((uint32_t)u, a.jt), n = fdiv(r, a.it);
+        return Tile{(int)n, (int)(r - n * a.it.d) * TR, (int)((uint32_t)u - r * a.jt.d) * 16};
     }
 
-    // window piece it of this lane: pixel (rr, cc) of the window, 16-byte
-    // piece pc; adjacent lanes on adjacent pieces
-    // piece it of a lane: window pixel px = (rr, cc), 16-byte piece pc;
-    // adjacent lanes on adjacent pieces; lanes past the last piece take the
-    // last piece again
-    struct Piece {
-        int px, pc, rr, cc;
-    };
-    static __device__ __forceinline__ Piece piece(int lane, int it) {
-        const int t = lane + 64 * it, tt = t < NX ? t : NX - 1;
-        const int px = tt / G, rr = px / XC;
-        return Piece{px, tt - px * G, rr, px - rr * XC};
-    }
-
-    // the piece's 16 bytes of image n at window origin (r0, c0), the
-    // position clamped into the image (the pieces outside are stored as
-    // zeros)
-    static __device__ __forceinline__ u32x4 load_piece(const Args &a, const Unit &un, const Piece &p) {
-        const int gr = clampi(2 * un.i - 2 + p.rr, 0, a.H - 1), gc = clampi(2 * un.j0 - 2 + p.cc, 0, a.W - 1);
-        const uint32_t pix = mul24((uint32_t)gr, (uint32_t)a.W) + (uint32_t)gc;
-        const uint16_t *xn = a.x + (size_t)un.n * a.H * a.W * C;
-        return *reinterpret_cast<const u32x4 *>(xn + (size_t)pix * C + p.pc * 8);
-    }
-
-    static __device__ __forceinline__ void load_window(const Args &a, int u, int lane, u32x4 (&xv)[NIT]) {
-        const Unit un = decode(a, u);
-#pragma unroll
-        for (int it = 0; it < NIT; it++)
-            xv[it] = load_piece(a, un, piece(lane, it));
-    }
-
-    // this unit's window into LDS; with PREF the next unit's pieces are
-    // loaded into the same registers as they are stored
-    static __device__ __forceinline__ void store_window(const Args &a, int u, int next, int lane, u32x4 (&xv)[NIT],
-                                                        uint8_t *X) {
-        const Unit un = decode(a, u), nx = decode(a, next);
-        const int r0 = 2 * un.i - 2, c0 = 2 * un.j0 - 2;
+    // this thread's pieces of a tile's window, positions clamped into the image
+    static __device__ __forceinline__ void load_window(const Args &a, int u, int tid, u32x4 (&xv)[NIT]) {
+        const Tile tl = decode(a, u);
+        const uint16_t *xn = a.x + (size_t)tl.n * a.H * a.W * C;
 #pragma unroll
         for (int it = 0; it < NIT; it++) {
-            const Piece p = piece(lane, it);
-            const int gr = r0 + p.rr, gc = c0 + p.cc;
+            const int t = min(tid + NT * it, NX - 1);
+            const int px = t / G, pc = t - px * G, rr = px / XC, cc = px - rr * XC;
+            const int gr = clampi(2 * tl.i0 - 2 + rr, 0, a.H - 1), gc = clampi(2 * tl.j0 - 2 + cc, 0, a.W - 1);
+            xv[it] = ld16(xn + ((size_t)gr * a.W + gc) * C + 8 * pc);
+        }
+    }
+    static __device__ __forceinline__ void store_window(const Args &a, const Tile &tl, int tid,
+                                                        const u32x4 (&xv)[NIT], uint8_t *X) {
+#pragma unroll
+        for (int it = 0; it < NIT; it++) {
+            const int t = tid + NT * it;
+            const int px = t / G, pc = t - px * G, rr = px / XC, cc = px - rr * XC;
+            const int gr = 2 * tl.i0 - 2 + rr, gc = 2 * tl.j0 - 2 + cc;
             const bool in = gr >= 0 && gr < a.H && gc >= 0 && gc < a.W;
-            *reinterpret_cast<u32x4 *>(X + (uint32_t)p.px * PP + (uint32_t)p.pc * 16) =
-                in ? xv[it] : u32x4{0u, 0u, 0u, 0u};
-            if (PREF)
-                xv[it] = load_piece(a, nx, p);
+            if (t < NX)
+                *reinterpret_cast<u32x4 *>(X + (uint32_t)px * PP + (uint32_t)pc * 16) = in ? xv[it] : u32x4{0u, 0u, 0u, 0u};
         }
     }
 
-    // the W1 and W2 pieces of hidden chunk kk in row-major lane order: lane
-    // 4r + p holds W1 row 32kk + 16t + r, columns 32ks + 8p .. + 7 (the
-    // fragment piece of lane (r, p)), and W2 row 16 ot + r, hidden
-    // 32kk + 4p .. + 3 and 32kk + 16 + 4p .. + 3.  Rows are clamped into the
-    // matrices; W1 columns past 2C meet zero tile entries.
-    static __device__ __forceinline__ void load_frag(const Args &a, int kk, int lr, int lp, Frag &f) {
-        const int R = a.R;
+    static __device__ __forceinline__ u32x4 permute(int idx, const u32x4 &v) {
+        u32x4 o;
 #pragma unroll
-        for (int t = 0; t < 2; t++) {
-            const int hr = min(32 * kk + 16 * t + lr, R - 1);
-            const uint16_t *wr = a.w1 + (size_t)hr * C2;
-#pragma unroll
-            for (int ks = 0; ks < KS; ks++) {
-                const int k = 32 * ks + 8 * lp;
-                f.w1[t][ks] = *reinterpret_cast<const u32x4 *>(wr + (k < C2 ? k : 0));
-            }
-        }
-        const int ha = 32 * kk + 4 * lp, hb = ha + 16 < R ? ha + 16 : ha;
-#pragma unroll
-        for (int ot = 0; ot < OTM; ot++) {
-            const uint16_t *wr = a.w2 + (size_t)min(16 * ot + lr, a.K - 1) * R;
-            f.w2[ot][0] = *reinterpret_cast<const u32x2 *>(wr + ha);
-            f.w2[ot][1] = *reinterpret_cast<const u32x2 *>(wr + hb);
-        }
-    }
-
-    static __device__ __forceinline__ uint32_t perm(int idx, uint32_t v) {
-        return (uint32_t)__builtin_amdgcn_ds_bpermute(idx, (int)v);
+        for (int d = 0; d < 4; d++)
+            o[d] = (uint32_t)__builtin_amdgcn_ds_bpermute(idx, (int)v[d]);
+        return o;
     }
 
     static __device__ void run(const Args &a, uint8_t *smem) {
         const int tid = threadIdx.x, lane = tid & 63;
         const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const int R = a.R, K = a.K;
+        const int q = lane >> 4, jl = lane & 15;
+        const int lr = lane >> 2, lp = lane & 3, pidx = (4 * jl + q) * 4;  // row-major lane, its fragment source
+        const int R = a.R, K = a.K, OT = (K + 15) / 16, HT = R / 16;
+        const uint32_t PH = w2_stride(R);  // LDS bytes per pixel of the hidden tile
+        u32x4 xv[NIT];
+        load_window(a, blockIdx.x, tid, xv);
         // the taps [3][3][C][8] and the vectors, once per workgroup
-        for (int i = tid; i < 9 * C; i += a.nw * 64)
-            *reinterpret_cast<u32x4 *>(smem + (uint32_t)i * 16) =
-                *reinterpret_cast<const u32x4 *>(a.gw + (size_t)i * 8);
+        for (int i = tid; i < 9 * C; i += NT)
+            *reinterpret_cast<u32x4 *>(smem + (uint32_t)i * 16) = ld16(a.gw + (size_t)i * 8);
         float *s0l = reinterpret_cast<float *>(smem + 9 * C * 16), *b0l = s0l + C, *s1l = b0l + C, *b1l = s1l + R,
               *s2l = b1l + R, *b2l = s2l + K;
-        for (int c = tid; c < C; c += a.nw * 64) {
+        for (int c = tid; c < C; c += NT) {
             s0l[c] = a.s0 ? a.s0[c] : 1.0f;
             b0l[c] = a.b0 ? a.b0[c] : 0.0f;
         }
-        for (int h = tid; h < R; h += a.nw * 64) {
+        for (int h = tid; h < R; h += NT) {
             s1l[h] = a.s1 ? a.s1[h] : 1.0f;
             b1l[h] = a.b1 ? a.b1[h] : 0.0f;
         }
-        for (int o = tid; o < K; o += a.nw * 64) {
+        for (int o = tid; o < K; o += NT) {
             s2l[o] = a.s2 ? a.s2[o] : 1.0f;
             b2l[o] = a.b2 ? a.b2[o] : 0.0f;
         }
         if constexpr (WL) {
-            // W1 [R][2C] and W2 [K][R] in 16-byte pieces, adjacent threads on
-            // adjacent pieces
-            for (int i = tid; i < R * (C / 4); i += a.nw * 64) {
-                const int r = i / (C / 4), pc = i - r * (C / 4);
-                *reinterpret_cast<u32x4 *>(smem + a.off_w1 + (uint32_t)r * w1_stride(C) + (uint32_t)pc * 16) =
-                    *reinterpret_cast<const u32x4 *>(a.w1 + (size_t)i * 8);
-            }
-            for (int i = tid; i < K * (R / 8); i += a.nw * 64) {
-                const int r = i / (R / 8), pc = i - r * (R / 8);
-                *reinterpret_cast<u32x4 *>(smem + a.off_w2 + (uint32_t)r * w2_stride(R) + (uint32_t)pc * 16) =
-                    *reinterpret_cast<const u32x4 *>(a.w2 + (size_t)i * 8);
-            }
+            // W1 [R][2C] and W2 [K][R] in 16-byte pieces, four in flight
+            auto stage = [&](const uint16_t *w, int rows, int pieces, uint32_t off, uint32_t stride) {
+                const int total = rows * pieces;
+                for (int i0 = tid; i0 < total; i0 += 4 * NT) {
+                    u32x4 v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; u++)
+                        v[u] = ld16(w + (size_t)min(i0 + NT * u, total - 1) * 8);
+#pragma unroll
+                    for (int u = 0; u < 4; u++) {
+                        const int i = i0 + NT * u, r = i / pieces, pc = i - r * pieces;
+                        if (i < total)
+                            *reinterpret_cast<u32x4 *>(smem + off + (uint32_t)r * stride + (uint32_t)pc * 16) = v[u];
+                    }
+                }
+            };
+            stage(a.w1, R, C / 4, a.off_w1, w1_stride(C));
+            stage(a.w2, K, R / 8, a.off_w2, w2_stride(R));
         }
-        __syncthreads();
-        int unit = (int)blockIdx.x * a.nw + wv;
-        if (unit >= a.units)
-            return;  // (after the workgroup's only barrier)
-        const int stride = (int)gridDim.x * a.nw;
-        const int H = a.H, W = a.W, NKK = (R + 31) / 32, OT = (K + 15) / 16;
-        uint8_t *X = smem + a.off_region + (uint32_t)wv * REGION, *V = X + XB, *Z = V + VB;
-        u32x4 xv[NIT];
-        load_window(a, unit, lane, xv);
-        for (;;) {
-            // every lane-dependent index is recomputed from an opaque copy of
-            // the lane index in every unit: hoisted out of the loop (one per
-            // window piece, conv operand and weight row) they would hold
-            // most of the registers for the whole kernel
-            int ln = lane;
-            asm volatile("" : "+v"(ln));
-            const int q = ln >> 4, jl = ln & 15;
-            const int lr = ln >> 2, lp = ln & 3, pidx = (4 * jl + q) * 4;  // row-major lane, its fragment source
-            const Unit un = decode(a, unit);
-            const int i = un.i, j0 = un.j0, r0 = 2 * i - 2, c0 = 2 * j0 - 2;
-            // 1. the window into LDS; the first FFN chunk's fragments and,
-            //    with few channels, the next unit's window in flight
-            const int next = unit + stride;
-            Frag f;
-            if constexpr (!WL)
-                load_frag(a, 0, lr, lp, f);
-            store_window(a, unit, next < a.units ? next : unit, ln, xv, X);
+        uint8_t *X = smem + a.off_x, *V = X + XB, *Z = smem + a.off_z, *Hd = X;
 
-            // 2. the grouped conv on the matrix unit (one group at a time:
-            //    an unrolled group loop hoists the LDS reads of later groups
-            //    and runs out of registers)
-#pragma unroll 1
-            for (int g = 0; g < G; g++) {
-                // A lane (row jl = 8s + o, K 8q .. 8q + 7): tap row q - s
-                const int di = q - (jl >> 3);
+        for (int u = (int)blockIdx.x; u < a.tiles; u += (int)gridDim.x) {
+            const Tile tl = decode(a, u);
+            const int H = a.H, W = a.W;
+            // 1. (the first time round also: the staged taps, vectors, weights)
+            store_window(a, tl, tid, xv, X);
+            __syncthreads();
+            if (u + (int)gridDim.x < a.tiles)
+                load_window(a, u + (int)gridDim.x, tid, xv);
+
+            // 2. the grouped conv: this wave's run of (group, position tile) items
+            {
+                constexpr int ITEMS = G * PT, PER = (ITEMS + NW - 1) / NW;
+                const int first = wv * PER, last = min(first + PER, ITEMS);
+                const int di = q - (jl >> 3);  // A lane (row jl = 8s + o, K 8q .. 8q + 7): tap row q - s
                 const bool tap = di >= 0 && di <= 2;
                 u32x4 av[3];
+                float4v sc, bi;
+                for (int item = first; item < last; item++) {
+                    const int g = item / PT, pt = item - g * PT;
+                    const int cd = 8 * g + 4 * (q & 1);  // channels of D lane rows 4q .. 4q + 3
+                    if (item == first || pt == 0) {  // wave-uniform
 #pragma unroll
-                for (int dj = 0; dj < 3; dj++) {
-                    const u32x4 v = *reinterpret_cast<const u32x4 *>(
-                        smem + (uint32_t)((((tap ? di : 0) * 3 + dj) * C + 8 * g + (jl & 7)) * 16));
-                    av[dj] = tap ? v : u32x4{0u, 0u, 0u, 0u};
-                }
-                // D lane (column jl, rows 4q .. 4q + 3): conv row w0 + (q >> 1),
-                // channels 8g + 4 (q & 1) .. + 3
-                const int cd = 8 * g + 4 * (q & 1);
-                float sc[4], bi[4];
-#pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    sc[e] = s0l[cd + e];
-                    bi[e] = b0l[cd + e];
-                }
-#pragma unroll
-                for (int rs = 0; rs < 2; rs++)
-#pragma unroll
-                    for (int ct = 0; ct < 3; ct++) {
-                        const int vc = 16 * ct + jl, vcl = vc < VC ? vc : VC - 1;  // columns past 32 are not kept
-                        const uint8_t *bp = X + (uint32_t)((rs + q) * XC + vcl) * PP + (uint32_t)g * 16;
-                        float4v d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int dj = 0; dj < 3; dj++)
-                            d = T::mfma(av[dj], *reinterpret_cast<const u32x4 *>(bp + dj * PP), d);
-                        if ((rs == 0 || q >= 2) && vc < VC)
-                            *reinterpret_cast<u32x2 *>(V + (uint32_t)((rs + (q >> 1)) * VC + vc) * PP +
-                                                       (uint32_t)cd * 2) =
-                                u32x2{T::pack2(fmaf(d[0], sc[0], bi[0]), fmaf(d[1], sc[1], bi[1])),
-                                      T::pack2(fmaf(d[2], sc[2], bi[2]), fmaf(d[3], sc[3], bi[3]))};
+                        for (int dj = 0; dj < 3; dj++) {
+                            const u32x4 v = *reinterpret_cast<const u32x4 *>(
+                                smem + (uint32_t)((((tap ? di : 0) * 3 + dj) * C + 8 * g + (jl & 7)) * 16));
+                            av[dj] = tap ? v : u32x4{0u, 0u, 0u, 0u};
+                        }
+                        sc = *reinterpret_cast<const float4v *>(s0l + cd);
+                        bi = *reinterpret_cast<const float4v *>(b0l + cd);
                     }
+                    const int pos = 16 * pt + jl, pp = min(pos, NPOS - 1);
+                    const int rp = pp / VC, vc = pp - rp * VC;
+                    // (the last pair's fourth row meets only the dropped
+                    // second row's taps)
+                    const uint8_t *bp = X + (uint32_t)(min(2 * rp + q, XR - 1) * XC + vc) * PP + (uint32_t)g * 16;
+                    float4v d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int dj = 0; dj < 3; dj++)
+                        d = T::mfma(av[dj], *reinterpret_cast<const u32x4 *>(bp + dj * PP), d);
+                    const int vr = 2 * rp + (q >> 1);
+                    if (pos < NPOS && vr < VR)
+                        *reinterpret_cast<u32x2 *>(V + (uint32_t)(vr * VC + vc) * PP + (uint32_t)cd * 2) =
+                            u32x2{T::pack2(fmaf(d[0], sc[0], bi[0]), fmaf(d[1], sc[1], bi[1])),
+                                  T::pack2(fmaf(d[2], sc[2], bi[2]), fmaf(d[3], sc[3], bi[3]))};
+                }
             }
+            __syncthreads();
 
-            // 3. BlurPool of the conv output and of the input (reflected
-            //    positions; the conv map sits one row and one column inside
-            //    the window) into the tile [16][C2P]
-            //    Lane-constant per pass: the pixel, the four channels, the
-            //    map they come from (its base and row stride); the rows'
-            //    reflections are wave-uniform.
-            const uint32_t xr0 = refl(2 * i - 1, H) - r0, xr1 = 2, xr2 = refl(2 * i + 1, H) - r0;
-#pragma unroll 2
-            for (int t = ln; t < UPX * (C2P / 4); t += 64) {
-                const int px = t / (C2P / 4), c = 4 * (t - px * (C2P / 4));
-                const bool cz = C2P == C2 || c < C2;      // zero padding past 2C
-                const int cc = cz ? c : 0;
-                const bool isv = cc < C;
-                const uint32_t base = isv ? (uint32_t)(V - X) - (uint32_t)(VC + 1) * PP + (uint32_t)cc * 2
-                                          : (uint32_t)(cc - C) * 2;
-                const uint32_t rst = isv ? (uint32_t)VC * PP : (uint32_t)XC * PP;
-                const uint32_t ro[3] = {mul24(xr0, rst), mul24(xr1, rst), mul24(xr2, rst)};
-                uint32_t co[3];
+            // 3. BlurPool of the conv output and of the input (the conv map
+            //    sits one row and one column inside the window), 8 channels
+            //    of a pixel per thread
+            for (int t = tid; t < 16 * TR * (C2P / 8); t += NT) {
+                const int px = t / (C2P / 8), c = 8 * (t - px * (C2P / 8));
+                const int i = tl.i0 + (px >> 4), j = tl.j0 + (px & 15);
+                u32x4 out = {0u, 0u, 0u, 0u};  // zero padding past 2C
+                if (c < C2) {
+                    const bool isv = c < C;
+                    const uint8_t *base = isv ? V + c * 2 : X + (c - C) * 2;
+                    const int ro = 2 * tl.i0 - (isv ? 1 : 2), co = 2 * tl.j0 - (isv ? 1 : 2), wd = isv ? VC : XC;
+                    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int tb = 0; tb < 3; tb++)
-                    co[tb] = mul24((uint32_t)(refl(2 * (j0 + px) + tb - 1, W) - c0), PP);
-                float acc[4] = {0.f, 0.f, 0.f, 0.f};
+                    for (int ta = 0; ta < 3; ta++) {
+                        const uint32_t rb = (uint32_t)((refl(2 * i + ta - 1, H) - ro) * wd);
 #pragma unroll
-                for (int ta = 0; ta < 3; ta++)
+                        for (int tb = 0; tb < 3; tb++) {
+                            const float wt = (ta == 1 ? 0.5f : 0.25f) * (tb == 1 ? 0.5f : 0.25f);
+                            const u32x4 v = *reinterpret_cast<const u32x4 *>(
+                                base + (rb + (uint32_t)(refl(2 * j + tb - 1, W) - co)) * PP);
 #pragma unroll
-                    for (int tb = 0; tb < 3; tb++) {
-                        const float wt = (ta == 1 ? 0.5f : 0.25f) * (tb == 1 ? 0.5f : 0.25f);
-                        const u32x2 v = *reinterpret_cast<const u32x2 *>(X + base + ro[ta] + co[tb]);
-                        acc[0] = fmaf(wt, T::lo(v[0]), acc[0]);
-                        acc[1] = fmaf(wt, T::hi(v[0]), acc[1]);
-                        acc[2] = fmaf(wt, T::lo(v[1]), acc[2]);
-                        acc[3] = fmaf(wt, T::hi(v[1]), acc[3]);
-                    }
-                *reinterpret_cast<u32x2 *>(Z + (uint32_t)px * PZ + (uint32_t)c * 2) =
-                    cz ? u32x2{T::pack2(acc[0], acc[1]), T::pack2(acc[2], acc[3])} : u32x2{0u, 0u};
-            }
-
-            // 4. the FFN
-            u32x4 zf[KS];
-#pragma unroll
-            for (int ks = 0; ks < KS; ks++)
-                zf[ks] = *reinterpret_cast<const u32x4 *>(Z + (uint32_t)jl * PZ + (uint32_t)(32 * ks + 8 * q) * 2);
-            float4v acc_o[OTM];
-#pragma unroll
-            for (int ot = 0; ot < OTM; ot++)
-                acc_o[ot] = float4v{0.f, 0.f, 0.f, 0.f};
-            auto chunk = [&](int kk) {
-                u32x4 w1f[2][KS], w2f[OTM];
-                if constexpr (WL) {
-                    // the fragments straight from the staged rows (clamped)
-#pragma unroll
-                    for (int t = 0; t < 2; t++) {
-                        const uint8_t *wr =
-                            smem + a.off_w1 + (uint32_t)min(32 * kk + 16 * t + jl, R - 1) * w1_stride(C);
-#pragma unroll
-                        for (int ks = 0; ks < KS; ks++) {
-                            const int k = 32 * ks + 8 * q;
-                            w1f[t][ks] = *reinterpret_cast<const u32x4 *>(wr + (k < C2 ? k : 0) * 2);
+                            for (int d = 0; d < 4; d++) {
+                                acc[2 * d] = fmaf(wt, T::lo(v[d]), acc[2 * d]);
+                                acc[2 * d + 1] = fmaf(wt, T::hi(v[d]), acc[2 * d + 1]);
+                            }
                         }
                     }
-                    const int ha = 32 * kk + 4 * q, hb = ha + 16 < R ? ha + 16 : ha;
 #pragma unroll
-                    for (int ot = 0; ot < OTM; ot++)
-                        if (ot < OT) {
-                            const uint8_t *wr =
-                                smem + a.off_w2 + (uint32_t)min(16 * ot + jl, K - 1) * w2_stride(R);
-                            const u32x2 pa = *reinterpret_cast<const u32x2 *>(wr + ha * 2),
-                                        pb = *reinterpret_cast<const u32x2 *>(wr + hb * 2);
-                            w2f[ot] = u32x4{pa[0], pa[1], pb[0], pb[1]};
-                        }
-                } else {
-                    // the fragments from the row-major pieces; then the next
-                    // chunk's pieces are loaded into the same registers
-#pragma unroll
-                    for (int t = 0; t < 2; t++)
-#pragma unroll
-                        for (int ks = 0; ks < KS; ks++)
-#pragma unroll
-                            for (int d = 0; d < 4; d++)
-                                w1f[t][ks][d] = perm(pidx, f.w1[t][ks][d]);
-#pragma unroll
-                    for (int ot = 0; ot < OTM; ot++)
-                        if (ot < OT)
-#pragma unroll
-                            for (int d = 0; d < 4; d++)
-                                w2f[ot][d] = perm(pidx, f.w2[ot][d >> 1][d & 1]);
-                    load_frag(a, min(kk + 1, NKK - 1), lr, lp, f);
+                    for (int d = 0; d < 4; d++)
+                        out[d] = T::pack2(acc[2 * d], acc[2 * d + 1]);
                 }
-                uint32_t hp[4];
+                *reinterpret_cast<u32x4 *>(Z + (uint32_t)px * PZ + (uint32_t)c * 2) = out;
+            }
+            __syncthreads();
+
+            // 4. expand: hidden tiles wv, wv + 8, ..
+            {
+                u32x4 zf[TR][KS];
 #pragma unroll
-                for (int t = 0; t < 2; t++) {
-                    const int h0 = 32 * kk + 16 * t;  // the expand tile's first hidden channel
-                    float4v u = {0.f, 0.f, 0.f, 0.f};
+                for (int t = 0; t < TR; t++)
 #pragma unroll
                     for (int ks = 0; ks < KS; ks++)
-                        u = T::mfma(w1f[t][ks], zf[ks], u);
-                    // lane (q, jl) holds hidden h0 + 4q + e of pixel jl; the
-                    // tile past R (R % 32 == 16) is zero
-                    const bool live = h0 < R;  // wave-uniform
-                    const int hh = live ? h0 + 4 * q : 0;
-                    const float4v sc = *reinterpret_cast<const float4v *>(s1l + hh),
-                                  bi = *reinterpret_cast<const float4v *>(b1l + hh);
+                        zf[t][ks] = *reinterpret_cast<const u32x4 *>(Z + (uint32_t)(16 * t + jl) * PZ +
+                                                                     (uint32_t)(32 * ks + 8 * q) * 2);
+                u32x4 wn[KS];  // the next tile's fragments (from global memory: row-major pieces)
+                auto fetch = [&](int ht) {
+                    const int r0 = 16 * min(ht, HT - 1);
 #pragma unroll
-                    for (int e2 = 0; e2 < 2; e2++) {
-                        float v[2];
+                    for (int ks = 0; ks < KS; ks++)
+                        if constexpr (WL)
+                            wn[ks] = *reinterpret_cast<const u32x4 *>(smem + a.off_w1 + (uint32_t)(r0 + jl) * w1_stride(C) +
+                                                                      min(32 * ks + 8 * q, C2 - 8) * 2);
+                        else
+                            wn[ks] = ld16(a.w1 + (size_t)(r0 + lr) * C2 + min(32 * ks + 8 * lp, C2 - 8));
+                };
+                fetch(wv);
+                for (int ht = wv; ht < HT; ht += NW) {
+                    u32x4 wf[KS];
 #pragma unroll
-                        for (int s = 0; s < 2; s++) {
-                            const int e = 2 * e2 + s;
-                            v[s] = live ? act_f(fmaf(u[e], sc[e], bi[e]), a.act) : 0.0f;
-                        }
-                        hp[2 * t + e2] = T::pack2(v[0], v[1]);
+                    for (int ks = 0; ks < KS; ks++)
+                        wf[ks] = WL ? wn[ks] : permute(pidx, wn[ks]);
+                    fetch(ht + NW);
+                    const float4v sc = *reinterpret_cast<const float4v *>(s1l + 16 * ht + 4 * q);
+                    const float4v bi = *reinterpret_cast<const float4v *>(b1l + 16 * ht + 4 * q);
+                    float4v h[TR];
+#pragma unroll
+                    for (int t = 0; t < TR; t++)
+                        h[t] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < KS; ks++)
+#pragma unroll
+                        for (int t = 0; t < TR; t++)
+                            h[t] = T::mfma(wf[ks], zf[t][ks], h[t]);
+#pragma unroll
+                    for (int t = 0; t < TR; t++) {
+                        float v[4];
+#pragma unroll
+                        for (int e = 0; e < 4; e++)
+                            v[e] = act_f(fmaf(h[t][e], sc[e], bi[e]), a.act);
+                        *reinterpret_cast<u32x2 *>(Hd + (uint32_t)(16 * t + jl) * PH + (uint32_t)(16 * ht + 4 * q) * 2) =
+                            u32x2{T::pack2(v[0], v[1]), T::pack2(v[2], v[3])};
                     }
                 }
-                const u32x4 ub = {hp[0], hp[1], hp[2], hp[3]};
+            }
+            __syncthreads();
+
+            // 5. project: the OT x TR products of 16 channels x 16 pixels dealt
+            //    evenly to the waves, in runs that share their W2 rows
+            {
+                const int n = OT * TR, u0 = wv * n / NW, u1 = (wv + 1) * n / NW;
+                const int NK = (R + 31) / 32;
+                for (int ot = u0 / TR; ot * TR < u1; ot++) {
+                    const int ta = u0 - ot * TR, tb = u1 - ot * TR;  // pixel rows ta <= t < tb
+                    float4v acc[TR];
 #pragma unroll
-                for (int ot = 0; ot < OTM; ot++)
-                    if (ot < OT)
-                        acc_o[ot] = T::mfma(w2f[ot], ub, acc_o[ot]);
-            };
-#pragma unroll 1
-            for (int kk = 0; kk < NKK; kk++)
-                chunk(kk);
-            // y = s2 * acc + b2: lane (q, jl) holds channels 16 ot + 4q .. + 3 of pixel j0 + jl
-            if (j0 + jl < a.Wo) {
-                uint16_t *yp = a.y + (((size_t)un.n * a.Ho + i) * a.Wo + j0 + jl) * K;
+                    for (int t = 0; t < TR; t++)
+                        acc[t] = float4v{0.f, 0.f, 0.f, 0.f};
+                    constexpr int KB = WL ? 2 : 4;  // K steps per batch, two batches of W2 in flight
+                    u32x4 wb[2][KB];
+                    const uint8_t *wl = smem + a.off_w2 + (uint32_t)min(16 * ot + jl, K - 1) * w2_stride(R);
+                    const uint16_t *wr = a.w2 + (size_t)min(16 * ot + lr, K - 1) * R;
+                    auto fetch = [&](int b, u32x4 (&w)[KB]) {
 #pragma unroll
-                for (int ot = 0; ot < OTM; ot++) {
+                        for (int k = 0; k < KB; k++)
+                            if constexpr (WL)
+                                w[k] = *reinterpret_cast<const u32x4 *>(wl + min(32 * (KB * b + k) + 8 * q, R - 8) * 2);
+                            else
+                                w[k] = ld16(wr + min(32 * (KB * b + k) + 8 * lp, R - 8));
+                    };
+                    auto use = [&](int b, const u32x4 (&w)[KB]) {
+                        // a K step past R (R % 32 == 16, or the batch's end) meets zeros
+                        u32x4 wf[KB];
+#pragma unroll
+                        for (int k = 0; k < KB; k++) {
+                            wf[k] = WL ? w[k] : permute(pidx, w[k]);
+                            if (32 * (KB * b + k) + 32 > R) {  // uniform
+                                const bool in = 32 * (KB * b + k) + 8 * q < R;
+#pragma unroll
+                                for (int d = 0; d < 4; d++)
+                                    wf[k][d] = in ? wf[k][d] : 0u;
+                            }
+                        }
+#pragma unroll
+                        for (int t = 0; t < TR; t++)
+                            if (t >= ta && t < tb) {  // uniform
+                                u32x4 hv[KB];
+                                const uint8_t *hp = Hd + (uint32_t)(16 * t + jl) * PH;
+#pragma unroll
+                                for (int k = 0; k < KB; k++)
+                                    hv[k] = *reinterpret_cast<const u32x4 *>(hp + min(32 * (KB * b + k) + 8 * q, R - 8) * 2);
+#pragma unroll
+                                for (int k = 0; k < KB; k++)
+                                    acc[t] = T::mfma(wf[k], hv[k], acc[t]);
+                            }
+                    };
+                    fetch(0, wb[0]);
+                    for (int b = 0; KB * b < NK; b += 2) {
+                        fetch(b + 1, wb[1]);
+                        use(b, wb[0]);
+                        if (KB * (b + 1) < NK) {
+                            fetch(b + 2, wb[0]);
+                            use(b + 1, wb[1]);
+                        }
+                    }
                     const int o = 16 * ot + 4 * q;
-                    if (o >= K)
-                        continue;
-                    float r[4];
+                    if (o < K) {
+                        const float4v sc = *reinterpret_cast<const float4v *>(s2l + o);
+                        const float4v bi = *reinterpret_cast<const float4v *>(b2l + o);
 #pragma unroll
-                    for (int e = 0; e < 4; e++)
-                        r[e] = fmaf(acc_o[ot][e], s2l[o + e], b2l[o + e]);
-                    *reinterpret_cast<u32x2 *>(yp + o) = u32x2{T::pack2(r[0], r[1]), T::pack2(r[2], r[3])};
+                        for (int t = 0; t < TR; t++)
+                            if (t >= ta && t < tb && tl.i0 + t < a.Ho && tl.j0 + jl < a.Wo) {
+                                float r[4];
+#pragma unroll
+                                for (int e = 0; e < 4; e++)
+                                    r[e] = fmaf(acc[t][e], sc[e], bi[e]);
+                                *reinterpret_cast<u32x2 *>(a.y + (((size_t)tl.n * a.Ho + tl.i0 + t) * a.Wo + tl.j0 + jl) * K + o) =
+                                    u32x2{T::pack2(r[0], r[1]), T::pack2(r[2], r[3])};
+                            }
+                    }
                 }
             }
-            if (next >= a.units)
-                break;
-            unit = next;
-            if (!PREF)
-                load_window(a, unit, ln, xv);
+            __syncthreads();  // the hidden tile's bytes are the next window's
         }
     }
 };
 
-template <typename T, int C, int OTM, bool WL>
-__global__ __launch_bounds__(256) void cfs2_kernel(Args a) {
+template <typename T, int C, int TR, bool WL, int WE>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WE, WE))) void cfs2_kernel(Args a) {
     extern __shared__ __attribute__((aligned(256))) uint8_t smem[];
-    Kern<T, C, OTM, WL>::run(a, smem);
+    Kern<T, C, TR, WL>::run(a, smem);
 }
 
-inline uint32_t region_for(int C) {
-    switch (C) {
-    case 16: return Kern<F16, 16, 4, false>::REGION;
-    case 24: return Kern<F16, 24, 4, false>::REGION;
-    case 32: return Kern<F16, 32, 4, false>::REGION;
-    case 48: return Kern<F16, 48, 4, false>::REGION;
-    case 64: return Kern<F16, 64, 4, false>::REGION;
-    default: return 0;
-    }
+// Tile height and whether the weights are staged.  In order: staged weights
+// with two workgroups on a CU (128 images of 128 x 128: C = 24 159 us, against
+// 206 with one workgroup and four rows; C = 16 83); four rows with the weights
+// (C = 32, 64 x 64: 60 us, against 74 without them and 68 with two rows); four
+// rows without (C = 48, 64 x 64: 89 us, against 97 with two rows and the
+// weights); two rows.  Fewer four-row tiles than CUs: two rows (4 images,
+// C = 64: 12.6 against 16.6 us).
+struct Plan {
+    int tr;
+    bool wl;
+    uint32_t lds;
+};
+constexpr uint32_t PAIR_LDS = 80 * 1024, FULL_LDS = 160 * 1024;
+// instances with registers for two workgroups on a CU
+constexpr bool pairs(int C, int TR, bool wl) { return wl && (C == 16 || (TR == 2 && C <= 48)); }
+
+inline Plan plan_for(int C, int R, int K, int64_t tiles4, int cus) {
+    const uint32_t st = staged_bytes(C, R, K), wb = weights_bytes(C, R, K);
+    auto need = [&](int tr, bool wl) { return st + (wl ? wb : 0u) + map_bytes(C, tr, R) + tile_bytes(C, tr); };
+    const int top = tiles4 < cus ? 2 : 4;
+    for (int tr = top; tr >= 2; tr -= 2)
+        if (pairs(C, tr, true) && need(tr, true) <= PAIR_LDS)
+            return Plan{tr, true, need(tr, true)};
+    for (int tr = top; tr >= 2; tr -= 2)
+        for (int wl = 1; wl >= 0; wl--)
+            if (need(tr, wl != 0) <= FULL_LDS)
+                return Plan{tr, wl != 0, need(tr, wl != 0)};
+    return Plan{0, false, 0};
 }
 
-// waves per workgroup (1 .. 4): the count that lets a compute unit's LDS
-// hold the most waves (every workgroup stages its own taps and vectors, and
-// the weights when wl); 0 when not even one wave fits.  *per_cu receives
-// that many waves.
-inline int waves_for(int C, int R, int K, bool wl, int *per_cu = nullptr) {
-    const uint32_t r = region_for(C), lds = 160u * 1024u;
-    const uint32_t st = staged_bytes(C, R, K) + (wl ? weights_bytes(C, R, K) : 0u);
-    int best = 0, best_waves = 0;
-    for (int nw = 1; r && nw <= 4; nw++) {
-        const uint32_t wg = st + (uint32_t)nw * r;
-        const int waves = wg <= lds ? nw * (int)(lds / wg) : 0;
-        if (waves >= best_waves && waves > 0) {
-            best = nw;
-            best_waves = waves;
-        }
-    }
-    if (per_cu)
-        *per_cu = best_waves;
-    return best;
-}
-
-// the weights go to LDS when that still leaves two waves per SIMD, or as
-// many waves as without them (measured: at 128 x 128 x 16, 8 waves with the
-// weights in LDS beat 10 without; at 64 x 64 x 32, 4 lose to 6)
-inline bool weights_in_lds(int C, int R, int K) {
-    int wl = 0, wg = 0;
-    waves_for(C, R, K, true, &wl);
-    waves_for(C, R, K, false, &wg);
-    return wl >= 1 && (wl >= 8 || wl >= wg);
-}
-
-template <typename T, int C, int OTM, bool WL>
-hipError_t launch_t(const Args &a, size_t lds, int grid, hipStream_t st) {
-    auto kf = cfs2_kernel<T, C, OTM, WL>;
-    hipError_t e = allow_full_lds((const void *)kf);
+template <typename T, int C, int TR, bool WL, int WE>
+hipError_t launch_e(const Args &a, size_t lds, int cus, hipStream_t st) {
+    const void *k = (const void *)cfs2_kernel<T, C, TR, WL, WE>;
+    hipError_t e = allow_full_lds(k);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(kf, dim3(grid), dim3(64 * a.nw), lds, st, a);
-    return hipGetLastError();
+    Args b = a;
+    void *args[] = {&b};
+    const int cap = cus * (WE / 2);  // persistent workgroups, WE / 2 per CU
+    return hipLaunchKernel(k, dim3(a.tiles < cap ? a.tiles : cap), dim3(NT), args, lds, st);
 }
 
-template <typename T, int C, bool WL>
-hipError_t launch_w(const Args &a, size_t lds, int grid, hipStream_t st) {
-    if (a.K <= 32)
-        return launch_t<T, C, 2, WL>(a, lds, grid, st);
-    return a.K <= 64 ? launch_t<T, C, 4, WL>(a, lds, grid, st) : launch_t<T, C, 8, WL>(a, lds, grid, st);
+template <typename T, int C, int TR, bool WL>
+hipError_t launch_t(const Args &a, size_t lds, int cus, hipStream_t st) {
+    if constexpr (pairs(C, TR, WL))
+        if (lds <= PAIR_LDS)
+            return launch_e<T, C, TR, WL, 4>(a, lds, cus, st);
+    return launch_e<T, C, TR, WL, 2>(a, lds, cus, st);
 }
 
 template <typename T, int C>
-hipError_t launch_k(const Args &a, bool wl, size_t lds, int grid, hipStream_t st) {
-    return wl ? launch_w<T, C, true>(a, lds, grid, st) : launch_w<T, C, false>(a, lds, grid, st);
+hipError_t launch_c(const Args &a, const Plan &p, int cus, hipStream_t st) {
+    if (p.tr == 4)
+        return p.wl ? launch_t<T, C, 4, true>(a, p.lds, cus, st) : launch_t<T, C, 4, false>(a, p.lds, cus, st);
+    return p.wl ? launch_t<T, C, 2, true>(a, p.lds, cus, st) : launch_t<T, C, 2, false>(a, p.lds, cus, st);
 }
 
 template <typename T>
-hipError_t launch_c(const Args &a, int C, bool wl, size_t lds, int grid, hipStream_t st) {
+hipError_t launch(const Args &a, int C, const Plan &p, int cus, hipStream_t st) {
     switch (C) {
-    case 16: return launch_k<T, 16>(a, wl, lds, grid, st);
-    case 24: return launch_k<T, 24>(a, wl, lds, grid, st);
-    case 32: return launch_k<T, 32>(a, wl, lds, grid, st);
-    case 48: return launch_k<T, 48>(a, wl, lds, grid, st);
-    case 64: return launch_k<T, 64>(a, wl, lds, grid, st);
+    case 16: return launch_c<T, 16>(a, p, cus, st);
+    case 24: return launch_c<T, 24>(a, p, cus, st);
+    case 32: return launch_c<T, 32>(a, p, cus, st);
+    case 48: return launch_c<T, 48>(a, p, cus, st);
+    case 64: return launch_c<T, 64>(a, p, cus, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -558,7 +512,7 @@ hipError_t launch_c(const Args &a, int C, bool wl, size_t lds, int grid, hipStre
 
 bool convfirst_s2_supported(int H, int W, int C, int R, int K) {
     return H >= 2 && W >= 2 && R >= 16 && R % 16 == 0 && R <= cfs2::RMAX && K >= 8 && K % 8 == 0 &&
-           K <= cfs2::KMAX && cfs2::waves_for(C, R, K, false) >= 1;
+           K <= cfs2::KMAX && (C == 16 || C == 24 || C == 32 || C == 48 || C == 64);
 }
 
 hipError_t launch_convfirst_s2(const void *x, void *y, const BlockW &w, int N, int H, int W, int C, int R, int K,
@@ -584,25 +538,21 @@ hipError_t launch_convfirst_s2(const void *x, void *y, const BlockW &w, int N, i
     a.R = R;
     a.K = K;
     a.act = act;
-    a.jt = (a.Wo + cfs2::UPX - 1) / cfs2::UPX;
-    const int64_t units = (int64_t)N * a.Ho * a.jt;
-    if (units <= 0)
-        return hipSuccess;
-    if (units > (int64_t)1 << 30)
+    const int cus = device_cu_count(), jt = (a.Wo + 15) / 16;
+    const cfs2::Plan p = cfs2::plan_for(C, R, K, (int64_t)N * ((a.Ho + 3) / 4) * jt, cus);
+    if (!p.tr)
+        return hipErrorInvalidConfiguration;
+    const int64_t tiles = (int64_t)N * ((a.Ho + p.tr - 1) / p.tr) * jt;
+    if ((int64_t)N * a.Ho * jt > (int64_t)1 << 30)
         return hipErrorInvalidValue;
-    a.units = (int)units;
-    const bool wl = cfs2::weights_in_lds(C, R, K);
-    a.nw = cfs2::waves_for(C, R, K, wl);
+    a.tiles = (int)tiles;
+    a.jt = make_fastdiv((uint32_t)jt);
+    a.it = make_fastdiv((uint32_t)((a.Ho + p.tr - 1) / p.tr));
     a.off_w1 = cfs2::staged_bytes(C, R, K);
     a.off_w2 = a.off_w1 + (uint32_t)R * cfs2::w1_stride(C);
-    a.off_region = a.off_w1 + (wl ? cfs2::weights_bytes(C, R, K) : 0u);
-    const size_t lds = a.off_region + (size_t)a.nw * cfs2::region_for(C);
-    // persistent workgroups: as many as the LDS lets every compute unit hold
-    const int per_cu = (int)((160u * 1024u) / lds);
-    const int64_t need = (a.units + a.nw - 1) / a.nw;
-    const int64_t cap = (int64_t)(per_cu > 0 ? per_cu : 1) * device_cu_count();
-    const int grid = (int)(need < cap ? need : cap);
-    return bf16 ? cfs2::launch_c<BF16>(a, C, wl, lds, grid, st) : cfs2::launch_c<F16>(a, C, wl, lds, grid, st);
+    a.off_x = a.off_w1 + (p.wl ? cfs2::weights_bytes(C, R, K) : 0u);
+    a.off_z = a.off_x + cfs2::map_bytes(C, p.tr, R);
+    return bf16 ? cfs2::launch<BF16>(a, C, p, cus, st) : cfs2::launch<F16>(a, C, p, cus, st);
 }
 
 }  // namespace cf

@@ -115,3 +115,21 @@ def test_convfirst_s2_paper_projection_shapes(name):
     y = run(x, p, w["act"])
     assert torch.isfinite(y.float()).all()
     assert_close(y.cpu()[SAMPLE], ref(x[SAMPLE], p, w["act"]), what=name, diag=DIAG_F16)
+
+
+@pytest.mark.parametrize("case", [
+    # C, R, K, N, H, W: enough tiles for four-row tiles in every plan
+    (16, 96, 32, 40, 37, 66),     # staged weights, two workgroups per CU, ragged rows and columns
+    (24, 144, 48, 90, 14, 70),    # two-row tiles, two workgroups per CU
+    (32, 192, 56, 90, 14, 70),    # four-row tiles with the weights, K % 16 == 8
+    (48, 272, 64, 90, 14, 70),    # four-row tiles, weights from L2, R % 32 == 16
+    (64, 1024, 128, 100, 9, 70),  # the largest R and K: two-row tiles, weights from L2
+    (48, 288, 64, 3, 9, 70),      # few tiles: two rows with the weights
+], ids=lambda c: "C%d_R%d_K%d_N%d_%dx%d" % c)
+def test_convfirst_s2_every_tile_plan(case):
+    C, R, K, N, H, W = case
+    say("convfirst_s2 plan", case)
+    x, p = make(286, N, H, W, C, R, K)
+    y = run(x, p)
+    pick = sorted({0, N // 2, N - 1})
+    assert_close(y.cpu()[pick], ref(x[pick], p), what="convfirst_s2 plan %s" % (case,), diag=DIAG_F16)
