@@ -13,6 +13,7 @@ I/O dtype and optional fp32 s0,b0 [C], s1,b1 [E*C], s2,b2 [C].
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 
 import torch
@@ -86,6 +87,83 @@ def library_path() -> str:
     return _LIB_PATH
 
 
+# Native argument checks (csrc/host/cf_args.cpp).  Each _*_fast function below
+# asks them whether a call's arguments are all as they should be and returns
+# what the library needs, or None: then, and where the module is not built, the
+# checks in Python run, which name what is wrong.
+def _load_args():
+    path = os.path.join(_PKG, "_lib", "_cf_args.so")
+    if not os.path.exists(path):
+        return None
+    spec = importlib.util.spec_from_file_location("_cf_args", path)
+    try:
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+    except ImportError:  # built against another torch
+        return None
+    return mod
+
+
+_args = _load_args()
+# key, weight, shape as indices into the sizes of the call; struct order
+if _args is not None:
+    # sizes: k, C, E*C
+    _BLOCK_SPEC = _args.spec((("dw_w", 1, (0, 0, 1)), ("s0", 0, (1,)), ("b0", 0, (1,)), ("w1", 1, (2, 1)),
+                              ("s1", 0, (2,)), ("b1", 0, (2,)), ("w2", 1, (1, 2)), ("s2", 0, (1,)), ("b2", 0, (1,))))
+    # sizes: k, C, E*C, 8
+    _GBLOCK_SPEC = _args.spec((("gw_w", 1, (0, 0, 1, 3)), ("s0", 0, (1,)), ("b0", 0, (1,)), ("w1", 1, (2, 1)),
+                               ("s1", 0, (2,)), ("b1", 0, (2,)), ("w2", 1, (1, 2)), ("s2", 0, (1,)),
+                               ("b2", 0, (1,))))
+    # sizes: k, C, R, 8, 2C, K
+    _CFS2_SPEC = _args.spec((("gw_w", 1, (0, 0, 1, 3)), ("s0", 0, (1,)), ("b0", 0, (1,)), ("w1", 1, (2, 4)),
+                             ("s1", 0, (2,)), ("b1", 0, (2,)), ("w2", 1, (5, 2)), ("s2", 0, (5,)), ("b2", 0, (5,))))
+    # sizes: k, C, E*C, 8, R, K
+    _MBCONV_SPEC = _args.spec((("w1", 1, (2, 1)), ("s1", 0, (2,)), ("b1", 0, (2,)), ("gw_w", 1, (0, 0, 2, 3)),
+                               ("s2", 0, (2,)), ("b2", 0, (2,)), ("wr", 1, (4, 2)), ("br", 0, (4,)),
+                               ("we", 1, (2, 4)), ("be", 0, (2,)), ("w2", 1, (5, 2)), ("s3", 0, (5,)),
+                               ("b3", 0, (5,))))
+    # sizes: Cout, 2, Cin
+    _DOWN_SPEC = _args.spec((("wd", 1, (0, 1, 1, 2)), ("sd", 0, (0,)), ("bd", 0, (0,))))
+    # sizes: C, 3
+    _STEM_SPEC = _args.spec((("sw", 1, (0, 1, 1, 1)), ("ss", 0, (0,)), ("sb", 0, (0,))))
+
+
+def _shape(p, key, dims):
+    """The shape of parameter `key` when it is a tensor of that many
+    dimensions, else None."""
+    sh = _args.shape(p, key)
+    return sh if sh is not None and len(sh) == dims else None
+
+
+def _y_fast(x, out, shape):
+    """(y, its address) for a call whose x is checked; None where out is not as
+    it should be."""
+    if out is None:
+        y = torch.empty(shape, dtype=x.dtype, device=x.device)
+        return y, y.data_ptr()
+    ptr = _args.like(x, out, shape)
+    return None if ptr is None else (out, ptr)
+
+
+def _block_fast(x, p):
+    """(N, H, W, C, dtype code, x's address, E, k, parameters) or None."""
+    d = None if _args is None else _args.tensor4(x)
+    dw, w1 = (None, None) if d is None else (_shape(p, "dw_w", 3), _shape(p, "w1", 2))
+    if dw is None or w1 is None or not w1[0] or w1[0] % d[3]:
+        return None
+    params = _args.collect(_BLOCK_SPEC, x, p, (dw[0], d[3], w1[0]))
+    return None if params is None else (*d, w1[0] // d[3], dw[0], params)
+
+
+def _gblock_fast(x, p, C):
+    """(E, k, parameters) of a grouped block with C channels or None."""
+    gw, w1 = _shape(p, "gw_w", 4), _shape(p, "w1", 2)
+    if gw is None or w1 is None or not w1[0] or w1[0] % C:
+        return None
+    params = _args.collect(_GBLOCK_SPEC, x, p, (gw[0], C, w1[0], GROUP_WIDTH))
+    return None if params is None else (w1[0] // C, gw[0], params)
+
+
 _lib = None
 
 
@@ -98,10 +176,8 @@ def lib():
                                "`python -m paper_2404_03617_amd.build`" % _LIB_PATH)
         L = ctypes.CDLL(_LIB_PATH)
         i, sz, vp = ctypes.c_int, ctypes.c_size_t, ctypes.c_void_p
-        bp, dp = ctypes.POINTER(_BlockParams), ctypes.POINTER(_DownParams)
-        gp = ctypes.POINTER(_GBlockParams)
-        mp = ctypes.POINTER(_MBConvParams)
-        sp = ctypes.POINTER(_StemParams)
+        # the parameter structs: a pointer to one, or its bytes
+        bp = dp = gp = mp = sp = vp
         sig = {
             "cf_block_forward": (i, [vp, vp, bp, i, i, i, i, i, i, i, i, vp]),
             "cf_stage_forward": (i, [vp, vp, vp, sz, bp, i, i, i, i, i, i, i, i, i, vp]),
@@ -144,13 +220,15 @@ def _check(status: int):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
+    """The handle of `stream`, or of the current device's current stream (read
+    without building a Stream object)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _dims(x: torch.Tensor):
@@ -235,6 +313,8 @@ def _out(x: torch.Tensor, out, shape=None):
     shape = tuple(x.shape) if shape is None else tuple(shape)
     if out is None:
         return torch.empty(shape, dtype=x.dtype, device=x.device)
+    if _args is not None and _args.like(x, out, shape) is not None:
+        return out
     _check_tensor("out", out, shape, x.dtype, x.device)
     return out
 
@@ -297,14 +377,19 @@ def block_forward(x: torch.Tensor, p: dict, act: str = "gelu", out: torch.Tensor
                   stream=None) -> torch.Tensor:
     """Fused ConvFirst block: y = x + FFN(dwconv(x)).  A wide block over few
     pixels takes scratch memory for its hidden split from torch's allocator."""
-    y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out)
+    f = _block_fast(x, p) if act in ACTS else None
+    yf = None if f is None else _y_fast(x, out, f[:4])
+    if yf is not None:
+        (N, H, W, C, dt, xp, E, k, bp), (y, yp) = f, yf
+    else:
+        y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out)
+        dt, xp, yp, bp = DTYPES[x.dtype], x.data_ptr(), y.data_ptr(), ctypes.byref(bp)
     ws = _scratch(x, _split_bytes(x, E * C), stream)
     if ws is not None:  # the hidden split beats every configuration the tuner knows
-        _check(lib().cf_stage_forward(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), ctypes.byref(bp), 1, N, H, W, C, E, k,
-                                      DTYPES[x.dtype], ACTS[act], _stream(stream)))
-        return y
-    _check(lib().cf_block_forward(_ptr(x), _ptr(y), ctypes.byref(bp), N, H, W, C, E, k,
-                                  DTYPES[x.dtype], ACTS[act], _stream(stream)))
+        _check(lib().cf_stage_forward(xp, yp, ws.data_ptr(), ws.numel(), bp, 1, N, H, W, C, E, k, dt, ACTS[act],
+                                      _stream(stream)))
+    else:
+        _check(lib().cf_block_forward(xp, yp, bp, N, H, W, C, E, k, dt, ACTS[act], _stream(stream)))
     return y
 
 
@@ -327,6 +412,23 @@ def block_tuned_config(x_shape, C: int, E: int, k: int, dtype=torch.float16, act
     return lib().cf_block_tuned_config(N, H, W, C, E, k, DTYPES[dtype], ACTS[act])
 
 
+def _prepare_stage(x: torch.Tensor, blocks: list, out):
+    """The checked arguments of a stage: (y, the blocks' structs, sizes)."""
+    fast = [_block_fast(x, b) for b in blocks]
+    if None not in fast and len({f[:8] for f in fast}) == 1:
+        N, H, W, C, _, _, E, k, _ = fast[0]
+        yf = _y_fast(x, out, (N, H, W, C))
+        if yf is not None:
+            return yf[0], b"".join(f[8] for f in fast), (N, H, W, C, E, k)
+    keep = []
+    structs = [_block_struct(x, b, keep) for b in blocks]
+    dims = {_block_shape(x, b) for b in blocks}
+    if len(dims) != 1:
+        raise ValueError("every block of a stage must have the same shape")
+    _check_device(x)
+    return _out(x, out), (_BlockParams * len(blocks))(*structs), dims.pop()
+
+
 def stage_forward(x: torch.Tensor, blocks: list, act: str = "gelu", out=None, ws=None,
                   stream=None) -> torch.Tensor:
     """`len(blocks)` fused blocks of one shape, ping-ponging through ws."""
@@ -334,18 +436,10 @@ def stage_forward(x: torch.Tensor, blocks: list, act: str = "gelu", out=None, ws
         raise ValueError("a stage needs at least one block")
     if act not in ACTS:
         raise ValueError("act must be one of %s" % sorted(ACTS))
-    keep = []
-    structs = [_block_struct(x, b, keep) for b in blocks]
-    dims = {_block_shape(x, b) for b in blocks}
-    if len(dims) != 1:
-        raise ValueError("every block of a stage must have the same shape")
-    N, H, W, C, E, k = dims.pop()
-    _check_device(x)
-    y = _out(x, out)
+    y, arr, (N, H, W, C, E, k) = _prepare_stage(x, blocks, out)
     L = lib()
     need = L.cf_stage_workspace_bytes(len(blocks), N, H, W, C, DTYPES[x.dtype])
     ws = _scratch(x, need + _split_bytes(x, E * C), stream) if ws is None else _workspace(x, ws, need)
-    arr = (_BlockParams * len(blocks))(*structs)
     _check(L.cf_stage_forward(_ptr(x), _ptr(y), _ptr(ws), 0 if ws is None else ws.numel(),
                               arr, len(blocks), N, H, W, C, E, k, DTYPES[x.dtype], ACTS[act],
                               _stream(stream)))
@@ -361,18 +455,10 @@ def stage_forward_microbatch(x: torch.Tensor, blocks: list, act: str = "gelu", m
         raise ValueError("a stage needs at least one block")
     if act not in ACTS:
         raise ValueError("act must be one of %s" % sorted(ACTS))
-    keep = []
-    structs = [_block_struct(x, b, keep) for b in blocks]
-    dims = {_block_shape(x, b) for b in blocks}
-    if len(dims) != 1:
-        raise ValueError("every block of a stage must have the same shape")
-    N, H, W, C, E, k = dims.pop()
-    _check_device(x)
-    y = _out(x, out)
+    y, arr, (N, H, W, C, E, k) = _prepare_stage(x, blocks, out)
     L = lib()
     need = L.cf_stage_microbatch_workspace_bytes(len(blocks), N, H, W, C, micro_batch, DTYPES[x.dtype])
     ws = _scratch(x, need + _split_bytes(x, E * C), stream) if ws is None else _workspace(x, ws, need)
-    arr = (_BlockParams * len(blocks))(*structs)
     _check(L.cf_stage_forward_microbatch(_ptr(x), _ptr(y), _ptr(ws), 0 if ws is None else ws.numel(), arr,
                                          len(blocks), N, H, W, C, E, k, micro_batch, DTYPES[x.dtype], ACTS[act],
                                          _stream(stream)))
@@ -381,6 +467,15 @@ def stage_forward_microbatch(x: torch.Tensor, blocks: list, act: str = "gelu", m
 
 def downsample_forward(x: torch.Tensor, p: dict, out=None, stream=None) -> torch.Tensor:
     """2x2 stride-2 conv: p has wd [Cout,2,2,Cin] and optional fp32 sd, bd [Cout]."""
+    d = None if _args is None else _args.tensor4(x)
+    wd = None if d is None else _shape(p, "wd", 4)
+    if wd is not None:
+        N, H, W, Cin, dt, xp = d
+        dp = _args.collect(_DOWN_SPEC, x, p, (wd[0], 2, Cin))
+        yf = None if dp is None else _y_fast(x, out, (N, H // 2, W // 2, wd[0]))
+        if yf is not None:
+            _check(lib().cf_downsample_forward(xp, yf[1], dp, N, H, W, Cin, wd[0], dt, _stream(stream)))
+            return yf[0]
     N, H, W, Cin = _dims(x)
     wd = p.get("wd")
     if not isinstance(wd, torch.Tensor) or wd.dim() != 4:
@@ -443,6 +538,13 @@ def gblock_forward(x: torch.Tensor, p: dict, act: str = "relu", out=None, stream
     s1,b1 [E*C], s2,b2 [C].  ReLU is the paper's activation."""
     if act not in ACTS:
         raise ValueError("act must be one of %s" % sorted(ACTS))
+    d = None if _args is None else _args.tensor4(x)
+    f = None if d is None else _gblock_fast(x, p, d[3])
+    yf = None if f is None else _y_fast(x, out, d[:4])
+    if yf is not None:
+        (N, H, W, C, dt, xp), (E, k, gp) = d, f
+        _check(lib().cf_gblock_forward(xp, yf[1], gp, N, H, W, C, E, k, dt, ACTS[act], _stream(stream)))
+        return yf[0]
     N, H, W, C = _dims(x)
     for key in ("gw_w", "w1", "w2"):
         if not isinstance(p.get(key), torch.Tensor):
@@ -492,6 +594,16 @@ def convfirst_s2_forward(x: torch.Tensor, p: dict, act: str = "relu", out=None, 
     Returns [N, ceil(H/2), ceil(W/2), K]; out must not overlap x."""
     if act not in ACTS:
         raise ValueError("act must be one of %s" % sorted(ACTS))
+    d = None if _args is None else _args.tensor4(x)
+    gw, w1, w2 = (None,) * 3 if d is None else (_shape(p, "gw_w", 4), _shape(p, "w1", 2), _shape(p, "w2", 2))
+    if gw is not None and w1 is not None and w2 is not None:
+        N, H, W, C, dt, xp = d
+        k, R, K = gw[0], w1[0], w2[0]
+        gp = _args.collect(_CFS2_SPEC, x, p, (k, C, R, GROUP_WIDTH, 2 * C, K))
+        yf = None if gp is None else _y_fast(x, out, (N, (H + 1) // 2, (W + 1) // 2, K))
+        if yf is not None:
+            _check(lib().cf_convfirst_s2_forward(xp, yf[1], gp, N, H, W, C, R, K, k, dt, ACTS[act], _stream(stream)))
+            return yf[0]
     N, H, W, C = _dims(x)
     for key in ("gw_w", "w1", "w2"):
         if not isinstance(p.get(key), torch.Tensor):
@@ -567,6 +679,17 @@ def stem_gblock_forward(x: torch.Tensor, stem: dict, p: dict, act: str = "relu",
     C = 16 or 32."""
     if act not in ACTS:
         raise ValueError("act must be one of %s" % sorted(ACTS))
+    d = None if _args is None else _args.tensor4(x)
+    sw = None if d is None or d[3] != 3 else _shape(stem, "sw", 4)
+    if sw is not None:
+        (N, H, W, _, dt, xp), C = d, sw[0]
+        sp = _args.collect(_STEM_SPEC, x, stem, (C, 3))
+        f = None if sp is None or not C else _gblock_fast(x, p, C)
+        yf = None if f is None else _y_fast(x, out, (N, (H + 1) // 2, (W + 1) // 2, C))
+        if yf is not None:
+            E, k, gp = f
+            _check(lib().cf_stem_gblock_forward(xp, yf[1], sp, gp, N, H, W, C, E, k, dt, ACTS[act], _stream(stream)))
+            return yf[0]
     N, H, W = _image_dims(x)
     if not isinstance(stem.get("sw"), torch.Tensor) or stem["sw"].dim() != 4:
         raise ValueError("stem parameter sw [C, 3, 3, 3] is required")
@@ -634,6 +757,15 @@ def _mbconv_args(x: torch.Tensor, p: dict, launch: str, stride2: bool):
     pointers and the tensors it points into (kept alive by the caller)."""
     if launch not in LAUNCHES:
         raise ValueError("launch must be one of %s" % sorted(LAUNCHES))
+    d = None if _args is None else _args.tensor4(x)
+    w1, gw, wr, w2 = (None,) * 4 if d is None else (_shape(p, "w1", 2), _shape(p, "gw_w", 4), _shape(p, "wr", 2),
+                                                    _shape(p, "w2", 2))
+    if w1 is not None and gw is not None and wr is not None and w2 is not None and w1[0] and w1[0] % d[3] == 0:
+        C, EC, R, k = d[3], w1[0], wr[0], gw[0]
+        K = w2[0] if stride2 else C
+        mp = _args.collect(_MBCONV_SPEC, x, p, (k, C, EC, GROUP_WIDTH, R, K))
+        if mp is not None:
+            return (*d[:4], EC // C, R, K, k), mp, None
     N, H, W, C = _dims(x)
     for key in ("w1", "gw_w", "wr", "we", "w2"):
         if not isinstance(p.get(key), torch.Tensor):
@@ -661,7 +793,7 @@ def _mbconv_args(x: torch.Tensor, p: dict, launch: str, stride2: bool):
             keep.append(t)
         vals[key] = None if t is None else t.data_ptr()
     _check_device(x)
-    return (N, H, W, C, EC // C, R, K, k), _MBConvParams(**vals), keep
+    return (N, H, W, C, EC // C, R, K, k), ctypes.byref(_MBConvParams(**vals)), keep
 
 
 def mbconv_forward(x: torch.Tensor, p: dict, out=None, ws=None, launch: str = "cooperative",
@@ -679,7 +811,7 @@ def mbconv_forward(x: torch.Tensor, p: dict, out=None, ws=None, launch: str = "c
         ws = _scratch(x, max(1, mbconv_workspace_bytes(N, H, W, C, E, R, x.dtype)), stream)
     else:
         _workspace(x, ws, 0)
-    _check(lib().cf_mbconv_forward(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), ctypes.byref(mp), N, H, W, C, E,
+    _check(lib().cf_mbconv_forward(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), mp, N, H, W, C, E,
                                    R, k, DTYPES[x.dtype], LAUNCHES[launch], _stream(stream)))
     return y
 
@@ -699,7 +831,7 @@ def mbconv_s2_forward(x: torch.Tensor, p: dict, out=None, ws=None, launch: str =
         ws = _scratch(x, max(1, mbconv_s2_workspace_bytes(N, H, W, C, E, R, K, x.dtype)), stream)
     else:
         _workspace(x, ws, 0)
-    _check(lib().cf_mbconv_s2_forward(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), ctypes.byref(mp), N, H, W, C, E,
+    _check(lib().cf_mbconv_s2_forward(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), mp, N, H, W, C, E,
                                       R, K, k, DTYPES[x.dtype], LAUNCHES[launch], _stream(stream)))
     return y
 

@@ -3,7 +3,9 @@
     python -m paper_2404_03617_amd.build        # or build() from Python
 
 Each csrc/*.hip file is compiled by hipcc for gfx950 into _build/, in
-parallel, then linked into paper_2404_03617_amd/_lib/libconvfirst.so.
+parallel, then linked into paper_2404_03617_amd/_lib/libconvfirst.so.  The
+binding's argument checks (csrc/host/cf_args.cpp, host code against torch's
+headers) become the CPython module _lib/_cf_args.so.
 """
 from __future__ import annotations
 
@@ -20,6 +22,8 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB_DIR = os.path.join(PKG, "_lib")
 LIB = os.path.join(LIB_DIR, "libconvfirst.so")
+ARGS_SRC = os.path.join(CSRC, "host", "cf_args.cpp")
+ARGS_LIB = os.path.join(LIB_DIR, "_cf_args.so")
 
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -43,14 +47,38 @@ def _compile(src: str) -> str:
     return obj
 
 
+def build_args() -> str:
+    """Compile the native argument checks; returns the module's path."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+
+    tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = ARGS_LIB + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), ARGS_SRC, "-o", tmp]
+    for d in include_paths() + [sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", d]
+    cmd += ["-L" + tlib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + tlib]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("compiling %s failed:\n%s\n%s" % (ARGS_SRC, " ".join(cmd), r.stderr[-8000:]))
+    os.replace(tmp, ARGS_LIB)
+    return ARGS_LIB
+
+
 def build(jobs: int | None = None) -> str:
-    """Compile every kernel source and link the shared library; returns its path."""
+    """Compile every kernel source and link the shared library, and the native
+    argument checks; returns the library's path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
     os.makedirs(LIB_DIR, exist_ok=True)
     srcs = sources()
     jobs = jobs or min(len(srcs), max(1, (os.cpu_count() or 4)))
     with cfut.ThreadPoolExecutor(jobs) as ex:
+        args = ex.submit(build_args)
         objs = list(ex.map(_compile, srcs))
+        args.result()
     tmp = LIB + ".tmp"
     # hipBLASLt: the two GEMMs of the wide-block path (cf_libgemm.hip)
     cmd = [HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC"] + objs + ["-L/opt/rocm/lib", "-lhipblaslt",
