@@ -1,7 +1,6 @@
 // cf_unfused.hip -- layer-by-layer kernels for gfx950: the comparison path
-// of Fig. f:convfirst-tensor-machine (a) (depth-wise conv, expand GEMM with
-// activation, project GEMM with residual, every intermediate through HBM) and
-// the 2x2 stride-2 down-sampling conv between stages.
+// of Fig. f:convfirst-tensor-machine (a): depth-wise conv, expand GEMM with
+// activation, project GEMM with residual, every intermediate through HBM.
 //
 // GEMM shape used throughout ("TN"): Out[p][o] = epi( sum_k A[p][k] * B[o][k] )
 // with both operands K-contiguous.  Computed transposed on MFMA 16x16x32
@@ -92,11 +91,10 @@ __global__ __launch_bounds__(256) void dw_kernel(const uint16_t *x, uint16_t *d,
 // LDS with a padded row stride against bank conflicts; LDS is double
 // buffered and the register copies run two K steps ahead, so two global
 // round trips are in flight while a step computes.
-enum { EPI_EXPAND = 0, EPI_PROJECT = 1, EPI_AFFINE = 2 };
-enum { A_PLAIN = 0, A_SPACE_TO_DEPTH = 1 };
+enum { EPI_EXPAND = 0, EPI_PROJECT = 1 };
 
 struct GemmArgs {
-    const uint16_t *a;   // A rows (pixels), K contiguous; or x for space-to-depth
+    const uint16_t *a;   // A rows (pixels), K contiguous
     const uint16_t *b;   // B rows (outputs), K contiguous
     uint16_t *out;       // [P][NO]
     const float *scale;  // [NO] or null
@@ -105,40 +103,9 @@ struct GemmArgs {
     int64_t P;
     int K, NO;
     int act;
-    // space-to-depth view: x is [N][2*Ho][2*Wo][Cin], row p = (n, i, j), K = 4*Cin
-    // (P < 2^31: 32-bit multiply-high division by Wo, Ho and Cin)
-    int Ho, Wo, Cin;
-    FastDiv divWo, divHo, divCin;
 };
 
-
-// Start of A row p (its K = 0 element): for the space-to-depth view,
-// k = (a*2 + b)*Cin + c reads x[n][2i+a][2j+b][c], and row p = (n, i, j)
-// starts at x[n][2i][2j][0]; a K step of GK never crosses a (a, b) boundary
-// (Cin is a multiple of GK), so a load is row start + tap offset + c.
-template <int AMODE>
-__device__ __forceinline__ const uint16_t *a_row_start(const GemmArgs &g, int64_t p) {
-    if constexpr (AMODE == A_PLAIN) {
-        return g.a + p * g.K;
-    } else {
-        const uint32_t pp = (uint32_t)p, ni = fdiv(pp, g.divWo), j = pp - ni * (uint32_t)g.Wo;
-        const uint32_t n = fdiv(ni, g.divHo), i = ni - n * (uint32_t)g.Ho;
-        const size_t W = 2 * (size_t)g.Wo;
-        return g.a + (((size_t)n * 2 * g.Ho + 2 * i) * W + 2 * j) * g.Cin;
-    }
-}
-// offset of element k from the row start
-template <int AMODE>
-__device__ __forceinline__ int64_t a_col_off(const GemmArgs &g, int k) {
-    if constexpr (AMODE == A_PLAIN) {
-        return k;
-    } else {
-        const int ab = (int)fdiv((uint32_t)k, g.divCin), c = k - ab * g.Cin;
-        return ((int64_t)(ab >> 1) * 2 * g.Wo + (ab & 1)) * g.Cin + c;
-    }
-}
-
-template <typename T, int BM, int BN, int GK, int EPI, int AMODE>
+template <typename T, int BM, int BN, int GK, int EPI>
 __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     constexpr int LDS_STRIDE = GK + 8;  // halves per LDS row (8 halves of padding)
     constexpr int WM = BM / 2, WN = BN / 2;  // per-wave tile (pixels x outputs)
@@ -167,15 +134,14 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     for (int q = 0; q < A_PIECES; q++) {
         const int64_t p = p0 + (q * 256 + tid) / (GK / 8);
         aok[q] = p < g.P;
-        arow[q] = a_row_start<AMODE>(g, aok[q] ? p : 0);
+        arow[q] = g.a + (aok[q] ? p : 0) * g.K;
     }
     u32x4 ra[A_PIECES], rbv[B_PIECES];
     auto load = [&](int k0) {
-        const int64_t koff = a_col_off<AMODE>(g, k0);
 #pragma unroll
         for (int q = 0; q < A_PIECES; q++) {
             const int c8 = (q * 256 + tid) % (GK / 8);
-            ra[q] = aok[q] ? *reinterpret_cast<const u32x4 *>(arow[q] + koff + c8 * 8) : u32x4{0u, 0u, 0u, 0u};
+            ra[q] = aok[q] ? *reinterpret_cast<const u32x4 *>(arow[q] + k0 + c8 * 8) : u32x4{0u, 0u, 0u, 0u};
         }
 #pragma unroll
         for (int q = 0; q < B_PIECES; q++) {
@@ -286,7 +252,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
                     else if (g.act == ACT_RELU)
                         v[e] = fmaxf(v[e], 0.f);
                 }
-            } else if constexpr (EPI == EPI_PROJECT) {
+            } else {
                 const u32x2 xr = *reinterpret_cast<const u32x2 *>(g.res + p * g.NO + o);
                 v[0] += T::lo(xr[0]);
                 v[1] += T::hi(xr[0]);
@@ -301,41 +267,17 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     }
 }
 
-template <typename T, int GK, int EPI, int AMODE>
-hipError_t gemm_k(const GemmArgs &g, hipStream_t st) {
-    // BN must divide NO; all NO used here are multiples of 64.  Where 128 x 128
-    // tiles would leave compute units short of work, 64-pixel tiles (the
-    // small weight operand is re-read, not the activations).
-    const int64_t tiles128 = ((g.P + 127) / 128) * (g.NO / 128);
-    if (g.NO % 128 == 0 && tiles128 >= 2 * device_cu_count()) {
+template <typename T, int EPI>
+hipError_t gemm(const GemmArgs &g, hipStream_t st) {
+    // BN must divide NO; all NO used here are multiples of 64
+    if (g.NO % 128 == 0) {
         dim3 grid((unsigned)((g.P + 127) / 128), g.NO / 128);
-        hipLaunchKernelGGL((gemm_kernel<T, 128, 128, GK, EPI, AMODE>), grid, dim3(256), 0, st, g);
-    } else if (g.NO % 128 == 0) {
-        dim3 grid((unsigned)((g.P + 63) / 64), g.NO / 128);
-        hipLaunchKernelGGL((gemm_kernel<T, 64, 128, GK, EPI, AMODE>), grid, dim3(256), 0, st, g);
+        hipLaunchKernelGGL((gemm_kernel<T, 128, 128, 32, EPI>), grid, dim3(256), 0, st, g);
     } else {
         dim3 grid((unsigned)((g.P + 127) / 128), g.NO / 64);
-        hipLaunchKernelGGL((gemm_kernel<T, 128, 64, GK, EPI, AMODE>), grid, dim3(256), 0, st, g);
+        hipLaunchKernelGGL((gemm_kernel<T, 128, 64, 32, EPI>), grid, dim3(256), 0, st, g);
     }
     return hipGetLastError();
-}
-
-template <typename T, int EPI, int AMODE>
-hipError_t gemm(const GemmArgs &g, hipStream_t st) {
-    if constexpr (AMODE == A_PLAIN) {
-        // layer-by-layer GEMMs (large P): 128-pixel tiles, K steps of 32
-        if (g.NO % 128 == 0) {
-            dim3 grid((unsigned)((g.P + 127) / 128), g.NO / 128);
-            hipLaunchKernelGGL((gemm_kernel<T, 128, 128, 32, EPI, AMODE>), grid, dim3(256), 0, st, g);
-        } else {
-            dim3 grid((unsigned)((g.P + 127) / 128), g.NO / 64);
-            hipLaunchKernelGGL((gemm_kernel<T, 128, 64, 32, EPI, AMODE>), grid, dim3(256), 0, st, g);
-        }
-        return hipGetLastError();
-    } else {
-        // down-sampling: K steps of 64 where Cin allows it
-        return g.Cin % 64 == 0 ? gemm_k<T, 64, EPI, AMODE>(g, st) : gemm_k<T, 32, EPI, AMODE>(g, st);
-    }
 }
 
 template <typename T>
@@ -377,7 +319,7 @@ hipError_t unfused(const void *x, void *y, void *d, void *h, const BlockW &w, co
     g1.K = s.C;
     g1.NO = EC;
     g1.act = s.act;
-    e = gemm<T, EPI_EXPAND, A_PLAIN>(g1, st);
+    e = gemm<T, EPI_EXPAND>(g1, st);
     if (e != hipSuccess)
         return e;
     GemmArgs g2{};
@@ -390,7 +332,7 @@ hipError_t unfused(const void *x, void *y, void *d, void *h, const BlockW &w, co
     g2.P = P;
     g2.K = EC;
     g2.NO = s.C;
-    return gemm<T, EPI_PROJECT, A_PLAIN>(g2, st);
+    return gemm<T, EPI_PROJECT>(g2, st);
 }
 
 }  // namespace
@@ -402,28 +344,6 @@ hipError_t launch_depthwise(const void *x, void *d, const BlockW &w, const Shape
 hipError_t launch_unfused_block(const void *x, void *y, void *d, void *h, const BlockW &w, const Shape &s,
                                 hipStream_t st) {
     return s.bf16 ? unfused<BF16>(x, y, d, h, w, s, st) : unfused<F16>(x, y, d, h, w, s, st);
-}
-
-hipError_t launch_downsample(const void *x, void *y, const void *wd, const float *sd, const float *bd, int N, int H,
-                             int W, int Cin, int Cout, int bf16, hipStream_t st) {
-    GemmArgs g{};
-    g.a = (const uint16_t *)x;
-    g.b = (const uint16_t *)wd;
-    g.out = (uint16_t *)y;
-    g.scale = sd;
-    g.bias = bd;
-    g.Ho = H / 2;
-    g.Wo = W / 2;
-    g.Cin = Cin;
-    g.P = (int64_t)N * g.Ho * g.Wo;
-    g.K = 4 * Cin;
-    g.NO = Cout;
-    if (g.P >= ((int64_t)1 << 31))
-        return hipErrorInvalidValue;
-    g.divWo = make_fastdiv((uint32_t)g.Wo);
-    g.divHo = make_fastdiv((uint32_t)g.Ho);
-    g.divCin = make_fastdiv((uint32_t)Cin);
-    return bf16 ? gemm<BF16, EPI_AFFINE, A_SPACE_TO_DEPTH>(g, st) : gemm<F16, EPI_AFFINE, A_SPACE_TO_DEPTH>(g, st);
 }
 
 }  // namespace cf
