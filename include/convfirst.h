@@ -60,9 +60,8 @@ typedef enum { CF_F16 = 0, CF_BF16 = 1 } cf_dtype;
 /* Activation phi after the expand layer (eq. e:ffn).  GELU is the exact
  * Gaussian-CDF form u * Phi(u).  The fused fp16 kernels evaluate it with a
  * packed-fp16 polynomial whose absolute error is below 3.4e-3 for |u| < 10
- * and zero beyond (it saturates to 0 and u); the fused bf16 kernels and the
- * layer-by-layer kernels use fp32 erf, the kernel for N*H*W <= 64 the fp32
- * erf of Abramowitz & Stegun 7.1.26 (|error| <= 1.5e-7).
+ * and zero beyond (it saturates to 0 and u); every other kernel uses the fp32
+ * erf or erfc of Abramowitz & Stegun 7.1.26 (|error| <= 1.5e-7).
  * CF_ACT_NONE makes the block affine (used by tests). */
 typedef enum { CF_ACT_GELU_ERF = 0, CF_ACT_RELU = 1, CF_ACT_NONE = 2 } cf_act;
 
