@@ -379,9 +379,7 @@ constexpr size_t SPLIT_PIXELS = 4096, SPLIT_BYTES = (size_t)16 << 20;
 // Hidden-layer groups for a batch `whole`, of which `part` runs per launch,
 // with `bytes` of room for the partials.
 static int fit_groups(const cf::Shape &whole, size_t bytes, const cf::Shape &part) {
-    const int g = cf::ffn_groups(whole);
-    const size_t one = (size_t)part.N * part.H * part.W * part.C * sizeof(float);
-    return (size_t)g * one <= bytes ? g : (int)(bytes / one);
+    return cf::ffn_fitting_groups(whole, (size_t)part.N * part.H * part.W * part.C * sizeof(float), bytes);
 }
 
 size_t cf_stage_workspace_bytes(int depth, int N, int H, int W, int C, cf_dtype dt) {

@@ -40,6 +40,7 @@
 // workspace is needed (with groups the sums are written by a later launch).
 #pragma once
 
+#include "cf_ffn_plan.h"
 #include "cf_fused_impl.h"
 
 namespace cf {
@@ -56,9 +57,6 @@ struct Args {
     int per;  // chunks per group
 };
 
-// shares of a chunk: one where two would not leave room for two slots
-constexpr int shares(int C) { return C == 512 ? 1 : 2; }
-constexpr int chunk(int C) { return 32 * shares(C); }  // hidden channels per step
 constexpr uint32_t PITCH = 1056;
 constexpr uint32_t slot_bytes(int C) { return (uint32_t)(C / 8 * shares(C)) * PITCH; }
 // LDS: two chunk slots, then s1 and b1 of the group's channels (fp16: a quarter of each)

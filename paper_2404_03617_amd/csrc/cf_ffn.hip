@@ -265,8 +265,7 @@ hipError_t block(const void *x, void *y, const BlockW &w, const Shape &s, int gr
     a.P = (uint32_t)((int64_t)s.N * s.H * s.W);
     a.EC = s.E * s.C;
     a.part = groups > 1 ? part : nullptr;
-    a.per = ceil_div(a.EC / chunk(s.C), groups);
-    groups = ceil_div(a.EC / chunk(s.C), a.per);
+    a.per = group_chunks(a.EC / chunk(s.C), groups);
     return s.act == ACT_GELU   ? ffn<T, ACT_GELU>(a, s.C, groups, st)
            : s.act == ACT_RELU ? ffn<T, ACT_RELU>(a, s.C, groups, st)
                                : ffn<T, ACT_NONE>(a, s.C, groups, st);
@@ -306,14 +305,18 @@ int ffn_groups(const Shape &s) {
     g = g > most ? most : g;
     const int64_t fit = ((int64_t)16 << 20) / (P * s.C * 4);
     g = g > fit ? fit : g;
-    if (g < 2)
-        return 1;
-    const int64_t per = (chunks + g - 1) / g;
-    return (int)((chunks + per - 1) / per);  // groups that are not empty
+    return ffn::filled_groups((int)chunks, (int)g);
+}
+
+int ffn_fitting_groups(const Shape &whole, size_t one, size_t bytes) {
+    const int g = ffn_groups(whole);
+    return g > 1 ? ffn::fitting_groups(whole.E * whole.C / ffn::chunk(whole.C), g, one, bytes) : 1;
 }
 
 hipError_t launch_ffn_block(const void *x, void *y, const BlockW &w, const Shape &s, int groups, float *part,
                             hipStream_t st) {
+    if (groups != ffn::filled_groups(s.E * s.C / ffn::chunk(s.C), groups))
+        return hipErrorInvalidValue;  // the caller adds as many partials as it asks for
     return s.bf16 ? ffn::block<BF16>(x, y, w, s, groups, part, st) : ffn::block<F16>(x, y, w, s, groups, part, st);
 }
 

@@ -89,9 +89,13 @@ hipError_t launch_slice(const void *x, void *y, const BlockW &w, const Shape &s,
 
 // Wide blocks as a depth-wise launch into y and the FFN in place (cf_ffn.h).
 // groups > 1: partial holds fp32 [groups][N*H*W][C]; the caller adds the
-// groups, b2 and x.  ffn_groups: how many a shape is worth, 1 for none.
+// groups, b2 and x.  ffn_groups: how many a shape is worth, 1 for none;
+// ffn_fitting_groups: those of `whole` whose partials of `one` bytes fit
+// `bytes`.  launch_ffn_block takes only a count that leaves no group empty, as
+// both return.
 bool ffn_applies(const Shape &s);
 int ffn_groups(const Shape &s);
+int ffn_fitting_groups(const Shape &whole, size_t one, size_t bytes);
 hipError_t launch_ffn_block(const void *x, void *y, const BlockW &w, const Shape &s, int groups, float *partial,
                             hipStream_t st);
 
