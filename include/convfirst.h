@@ -60,7 +60,8 @@ typedef enum { CF_F16 = 0, CF_BF16 = 1 } cf_dtype;
 /* Activation phi after the expand layer (eq. e:ffn).  GELU is the exact
  * Gaussian-CDF form u * Phi(u).  The fused fp16 kernels evaluate it with a
  * packed-fp16 polynomial whose absolute error is below 3.4e-3 for |u| < 10
- * and zero beyond (it saturates to 0 and u); every other kernel uses the fp32
+ * and zero beyond (it saturates to 0 and u); every other kernel, blocks with
+ * hidden groups (cf_stage_forward) in fp16 among them, uses the fp32
  * erf or erfc of Abramowitz & Stegun 7.1.26 (|error| <= 1.5e-7).
  * CF_ACT_NONE makes the block affine (used by tests). */
 typedef enum { CF_ACT_GELU_ERF = 0, CF_ACT_RELU = 1, CF_ACT_NONE = 2 } cf_act;
@@ -115,7 +116,10 @@ cf_status cf_block_forward(const void *x, void *y, const cf_block_params *p,
  * Otherwise, at C = 256 and 512 over few pixels, each block splits its hidden
  * layer over as many groups of workgroups as the room behind the minimum holds
  * (4*N*H*W*C bytes a group; a larger ws than recommended is used as well).
- * Results identical up to fp32 summation order, deterministic.
+ * With any number of groups results are identical up to fp32 summation order;
+ * without, a C = 512 or C = 256 fp16 block above 64 pixels takes the packed
+ * GELU polynomial (and for k >= 5 sums the rows of the depth-wise window in
+ * fp16), where with groups both are fp32.  Deterministic.
  * The library GEMMs are given no workspace of their own. */
 cf_status cf_stage_forward(const void *x, void *y, void *ws, size_t ws_bytes,
                            const cf_block_params *blocks, int depth,
@@ -132,9 +136,9 @@ size_t cf_stage_workspace_bytes(int depth, int N, int H, int W, int C, cf_dtype 
  * pixel range the same workgroup index, hence the same L2 (XCD), so a
  * micro-batch whose activations fit the L2s is read back from them; one that
  * fits the 256 MiB Infinity Cache is read back from it.  Only the stage's
- * input and output need DRAM.  Results equal cf_stage_forward's up to the
- * fp32 summation order of the hidden split (the same groups where both
- * workspaces hold them, behind the minimum here too).  micro_batch <= 0 picks a default: the largest micro-batch whose
+ * input and output need DRAM.  Results equal cf_stage_forward's where both
+ * have hidden groups, up to the fp32 summation order (the same groups where
+ * both workspaces hold them, behind the minimum here too), or both have none.  micro_batch <= 0 picks a default: the largest micro-batch whose
  * input and output activations fit 128 MiB (the whole batch whenever the
  * stage's activations already fit the Infinity Cache); a micro_batch >= N
  * runs the whole batch per block.  ws needs cf_stage_microbatch_workspace_bytes() bytes: two

@@ -197,10 +197,11 @@ hipError_t dw_launch(const void *x, void *d, const BlockW &w, const Shape &s, hi
 }
 
 template <typename T>
-hipError_t depthwise(const void *x, void *d, const BlockW &w, const Shape &s, hipStream_t st) {
+hipError_t depthwise(const void *x, void *d, const BlockW &w, const Shape &s, bool grouped, hipStream_t st) {
     // both kernels add in the same order where a row is summed in fp32, so a
-    // micro-batch gives the bits of its whole batch
-    if ((int64_t)s.N * s.H * s.W <= FEW_PIXELS && (T::is_bf16 || s.k < 5))
+    // micro-batch gives the bits of its whole batch; a block with hidden groups
+    // always sums in fp32 (as the kernels of a handful of pixels do)
+    if (grouped || ((int64_t)s.N * s.H * s.W <= FEW_PIXELS && (T::is_bf16 || s.k < 5)))
         switch (s.k) {
         case 1: return dw_launch<T, 1, 0>(x, d, w, s, st);
         case 3: return dw_launch<T, 3, 0>(x, d, w, s, st);
@@ -232,6 +233,10 @@ hipError_t ffn_launch(const Args &a, int groups, hipStream_t st) {
 
 template <typename T, int ACT>
 hipError_t ffn(const Args &a, int C, int groups, hipStream_t st) {
+    if constexpr (!T::is_bf16 && ACT == ACT_GELU)
+        if (groups > 1)
+            return C == 512 ? ffn_launch<T, 512, 1, 4, ACT_GELU_F32>(a, groups, st)
+                            : ffn_launch<T, 256, 1, 2, ACT_GELU_F32>(a, groups, st);
     if (C == 512)
         return ffn_launch<T, 512, 1, 4, ACT>(a, groups, st);
     if (C == 128)
@@ -250,7 +255,7 @@ hipError_t ffn(const Args &a, int C, int groups, hipStream_t st) {
 
 template <typename T>
 hipError_t block(const void *x, void *y, const BlockW &w, const Shape &s, int groups, float *part, hipStream_t st) {
-    hipError_t e = depthwise<T>(x, y, w, s, st);
+    hipError_t e = depthwise<T>(x, y, w, s, groups > 1, st);
     if (e != hipSuccess)
         return e;
     Args a{};
