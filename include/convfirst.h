@@ -61,8 +61,9 @@ typedef enum { CF_F16 = 0, CF_BF16 = 1 } cf_dtype;
  * Gaussian-CDF form u * Phi(u).  The fused fp16 kernels evaluate it with a
  * packed-fp16 polynomial whose absolute error is below 3.4e-3 for |u| < 10
  * and zero beyond (it saturates to 0 and u); every other kernel, blocks with
- * hidden groups (cf_stage_forward) in fp16 among them, uses the fp32
- * erf or erfc of Abramowitz & Stegun 7.1.26 (|error| <= 1.5e-7).
+ * hidden groups (cf_stage_forward) in fp16 among them, works in fp32 with an
+ * error below 1e-7 max(1, |u|) (the kernel for N*H*W <= 64: 3e-7, by the erf of
+ * Abramowitz & Stegun 7.1.26).
  * CF_ACT_NONE makes the block affine (used by tests). */
 typedef enum { CF_ACT_GELU_ERF = 0, CF_ACT_RELU = 1, CF_ACT_NONE = 2 } cf_act;
 

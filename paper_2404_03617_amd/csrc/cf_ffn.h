@@ -255,8 +255,8 @@ __global__ __launch_bounds__(PG * shares(C) * 64) __attribute__((amdgpu_waves_pe
                         v = T::pack2(u0, u1);
                     } else {
                         if constexpr (ACT == ACT_GELU_F32) {
-                            u0 = 0.25f * gelu_f32(4.0f * u0);
-                            u1 = 0.25f * gelu_f32(4.0f * u1);
+                            u0 = gelu_f32<4>(u0);
+                            u1 = gelu_f32<4>(u1);
                         }
                         half2v h = __builtin_bit_cast(half2v, T::pack2(u0, u1));
                         if constexpr (ACT == ACT_GELU)

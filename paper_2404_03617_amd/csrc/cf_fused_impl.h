@@ -255,7 +255,7 @@ __device__ __forceinline__ uint32_t act_q(float a, float b) {
             w.y = (_Float16)b;
             return __builtin_bit_cast(uint32_t, gelu_pk_f16_quarter(w));
         } else {
-            return T::pack2(0.25f * gelu_f32(4.0f * a), 0.25f * gelu_f32(4.0f * b));
+            return T::pack2(gelu_f32<4>(a), gelu_f32<4>(b));
         }
     } else if constexpr (ACT == ACT_RELU) {
         if constexpr (!T::is_bf16) {

@@ -1,4 +1,4 @@
-"""Generator of the packed-fp16 GELU coefficients of cf_device.h.
+"""Generator of the GELU coefficients of cf_device.h.
 
 The fused kernel evaluates GELU on fp16 pairs in the scaled variable
 w = u / 4 (the hidden activations are kept at a quarter of their value so
@@ -12,13 +12,17 @@ Step 1 fits Q by iteratively reweighted least squares towards the minimax
 error of u * (P - Phi) over |u| <= A.  Step 2 refines the coefficients by a
 Nelder-Mead search on the error of the exact fp16 evaluation (every rounding
 of the device sequence emulated) over every finite fp16 w with |4 w| < 10.
+The fp32 GELU is max(u, 0) - |u| q(t) exp(-u^2 / 2) with t = 1 / (1 + 0.32 |u|)
+and q a polynomial of degree 5, fitted the same way to
+erfc(x) exp(x^2) / 2, x = |u| / sqrt 2, towards the minimax error of the product.
+
 Prints the coefficients and the error figures quoted in cf_device.h.
 
     python gelu_fit.py
 """
 import numpy as np
 from scipy.optimize import minimize
-from scipy.special import erf
+from scipy.special import erf, erfcx
 
 A = 3.5       # fit range in u
 DEG = 4       # degree of Q in w*w
@@ -75,6 +79,24 @@ def errors(c):
     return err[inner].max(), (err[~inner] / np.abs(u[~inner])).max(), int(np.isnan(g).sum())
 
 
+def fp32_fit(p=0.32, n=6, iters=400):
+    """(c0 .. c(n-1), minimax error): see the top of the file."""
+    x = 5.0 + 5.0 * np.cos(np.linspace(0.0, np.pi, 4001))
+    g = 0.5 * erfcx(x / np.sqrt(2.0))
+    basis = np.stack([(1.0 + p * x) ** -float(j) for j in range(n)], 1)
+    weight = np.maximum(x, 0.3) * np.exp(-x * x / 2)
+    w, best, coef = np.ones_like(x), np.inf, None
+    for _ in range(iters):
+        sw = np.sqrt(w) * weight
+        c, *_ = np.linalg.lstsq(basis * sw[:, None], g * sw, rcond=None)
+        e = np.abs(basis @ c - g) * weight
+        if e.max() < best:
+            best, coef = e.max(), c
+        w = w * (e / e.max()) ** 0.7 + 1e-14
+        w /= w.sum()
+    return coef, best
+
+
 def main():
     c0 = irls()
     w = all_f16()
@@ -91,6 +113,8 @@ def main():
     e_in, e_out, nans = errors(c)
     print("coefficients c0..c4:", ", ".join("%.8f" % x for x in c))
     print("max |error| for |u| < 10: %.2e;  max |error| / |u| beyond: %.2e;  NaNs: %d" % (e_in, e_out, nans))
+    c, e = fp32_fit()
+    print("fp32 coefficients c0..c5:", ", ".join("%.9f" % x for x in c), " minimax error %.1e" % e)
 
 
 if __name__ == "__main__":

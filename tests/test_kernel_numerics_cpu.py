@@ -242,41 +242,64 @@ def test_slice_gelu_bound_catches_a_wrong_coefficient():
     assert _slice_gelu_max_error(bad) > 3e-7
 
 
-# ---- the fp32 GELU of cf_device.h: erfc by Abramowitz & Stegun 7.1.26
+# ---- the fp32 GELU of cf_device.h
 def device_gelu_constants():
-    """(p / sqrt 2, a5 .. a1 halved, -log2(e) / 2, cap) as the header writes them."""
+    """(p, c5 .. c0, -log2(e) / 2, cap) as the header writes them."""
     src = open(DEVICE_H).read()
     body = src[src.index("float gelu_f32(float u)"):]
     body = body[:body.index("\n}\n")]
     nums = [float(v) for v in re.findall(r"(-?\d+\.\d+)f", body)]
-    # in source order: p', 1.0, a5, a4, a3, a2, a1, -log2(e)/2, cap, 0.0
-    assert len(nums) == 10 and nums[1] == 1.0 and nums[9] == 0.0, nums
-    return [nums[0]] + nums[2:9]
+    # in source order: p, 1.0, c5 .. c0, -log2(e)/2, cap, 0.0
+    assert len(nums) == 11 and nums[1] == 1.0 and nums[10] == 0.0, nums
+    return [nums[0]] + nums[2:10]
 
 
 def device_gelu(u, nums):
-    p, a5, a4, a3, a2, a1, l2e, cap = [float(f32(v)) for v in nums]
+    """The kernel's sequence in float32 (each operation rounded once; the
+    reciprocal and exponential as correctly rounded float32 results)."""
+    nums = [float(f32(v)) for v in nums]
+    p, coef, l2e, cap = nums[0], nums[1:7], nums[7], nums[8]
     u = f32(u)
     t = f32(1.0 / f32(np.abs(u) * p + 1.0))
-    q = f32(a5 * t + a4)
-    for c in (a3, a2, a1):
+    q = coef[0]
+    for c in coef[1:]:
         q = f32(q * t + c)
-    q = f32(q * t)
     with np.errstate(under="ignore", over="ignore"):
         q = f32(q * f32(np.exp2(f32(f32(u * u) * l2e))))
     return f32(-np.minimum(np.abs(u), cap) * q + np.maximum(u, 0.0))
 
 
-def test_device_gelu_meets_the_erfc_bound_and_keeps_infinities():
+def erff_gelu(u):
+    """0.5 u (1 + erff(u / sqrt 2)) in float32, erff correctly rounded."""
+    from scipy.special import erf
+    u = f32(u)
+    return f32(f32(0.5 * u) * f32(1.0 + f32(erf(f32(u * f32(np.sqrt(0.5)))))))
+
+
+def wide_gelu(u):
+    """u Phi(u) without cancellation in the negative tail."""
+    from scipy.special import erfc
+    return f32(u) * 0.5 * erfc(-f32(u) / math.sqrt(2.0))
+
+
+def test_device_gelu_is_as_exact_as_the_erff_form_and_keeps_infinities():
     nums = device_gelu_constants()
-    want = [0.3275911 / math.sqrt(2)] + [v / 2 for v in (1.061405429, -1.453152027, 1.421413741, -0.284496736,
-                                                         0.254829592)] + [-0.5 * math.log2(math.e)]
-    assert np.allclose(nums[:7], want, rtol=2e-9, atol=0)
+    assert abs(nums[7] + 0.5 * math.log2(math.e)) < 1e-9
     u = np.concatenate([np.linspace(-12.0, 12.0, 480001), np.array([-1e4, -50.0, 50.0, 1e4, 1e-30, -1e-30, 0.0])])
-    err = np.max(np.abs(device_gelu(u, nums) - exact_gelu(u)) / np.maximum(1.0, np.abs(u)))
-    assert err < 3e-7, err
+    normal = np.random.default_rng(0).standard_normal(400000)
+    got, ref, old = device_gelu(u, nums), wide_gelu(u), erff_gelu(u)
+    worst = np.max(np.abs(got - ref) / np.maximum(1.0, np.abs(u)))
+    assert worst < 1e-7 and worst <= np.max(np.abs(old - ref) / np.maximum(1.0, np.abs(u)))
+
+    def rms(fn, v):
+        return np.sqrt(np.mean((fn(v) - wide_gelu(v)) ** 2))
+
+    for v in (u[:480001], normal):
+        assert rms(lambda z: device_gelu(z, nums), v) <= rms(erff_gelu, v)
+    tail = (u > -6.0) & (u < -1.0)
+    assert np.all(np.abs(got[tail] - ref[tail]) < 1e-6 * np.abs(ref[tail]) + 1.6e-8)
     with np.errstate(all="ignore"):
         assert device_gelu(np.array([3e38]), nums)[0] == float(f32(3e38))
     bad = list(nums)
     bad[1] *= 1.001
-    assert np.max(np.abs(device_gelu(u, bad) - exact_gelu(u)) / np.maximum(1.0, np.abs(u))) > 3e-7
+    assert np.max(np.abs(device_gelu(u, bad) - ref) / np.maximum(1.0, np.abs(u))) > 1e-7
