@@ -449,7 +449,7 @@ cf_status cf_stage_forward(const void *x, void *y, void *ws, size_t ws_bytes, co
         if (g > 1 && !overlap((char *)ws + need, pbytes, x, bytes) && !overlap((char *)ws + need, pbytes, y, bytes)) {
             groups = g;
             partial = (float *)((char *)ws + need);
-            sb.cfg = cf::CFG_FFN;
+            sb.cfg = cf::ffn_group_cfg(s);
         }
     }
     // block i writes y when (depth-1-i) is even, else ws, so the last one lands in y
@@ -547,7 +547,7 @@ cf_status cf_stage_forward_microbatch(const void *x, void *y, void *ws, size_t w
         if (s.cfg != cf::CFG_GENERIC && !cf::ffn_applies(whole) && cf::ffn_applies(s))
             s.cfg = cf::CFG_SINGLE;
         if (groups > 1)
-            s.cfg = cf::CFG_FFN;
+            s.cfg = cf::ffn_group_cfg(whole);
         const void *in = (const char *)x + (size_t)n0 * img;
         for (int i = 0; i < depth; i++) {
             void *out = (i == depth - 1) ? (void *)((char *)y + (size_t)n0 * img) : (void *)buf[i & 1];

@@ -232,9 +232,9 @@ hipError_t ffn_launch(const Args &a, int groups, hipStream_t st) {
 }
 
 template <typename T, int ACT>
-hipError_t ffn(const Args &a, int C, int groups, hipStream_t st) {
+hipError_t ffn(const Args &a, int C, int groups, bool f32, hipStream_t st) {
     if constexpr (!T::is_bf16 && ACT == ACT_GELU)
-        if (groups > 1)
+        if (f32)
             return C == 512 ? ffn_launch<T, 512, 1, 4, ACT_GELU_F32>(a, groups, st)
                             : ffn_launch<T, 256, 1, 2, ACT_GELU_F32>(a, groups, st);
     if (C == 512)
@@ -271,9 +271,10 @@ hipError_t block(const void *x, void *y, const BlockW &w, const Shape &s, int gr
     a.EC = s.E * s.C;
     a.part = groups > 1 ? part : nullptr;
     a.per = group_chunks(a.EC / chunk(s.C), groups);
-    return s.act == ACT_GELU   ? ffn<T, ACT_GELU>(a, s.C, groups, st)
-           : s.act == ACT_RELU ? ffn<T, ACT_RELU>(a, s.C, groups, st)
-                               : ffn<T, ACT_NONE>(a, s.C, groups, st);
+    const bool f32 = s.cfg == CFG_FFN_F32;
+    return s.act == ACT_GELU   ? ffn<T, ACT_GELU>(a, s.C, groups, f32, st)
+           : s.act == ACT_RELU ? ffn<T, ACT_RELU>(a, s.C, groups, f32, st)
+                               : ffn<T, ACT_NONE>(a, s.C, groups, f32, st);
 }
 
 }  // namespace ffn
@@ -316,6 +317,16 @@ int ffn_groups(const Shape &s) {
 int ffn_fitting_groups(const Shape &whole, size_t one, size_t bytes) {
     const int g = ffn_groups(whole);
     return g > 1 ? ffn::fitting_groups(whole.E * whole.C / ffn::chunk(whole.C), g, one, bytes) : 1;
+}
+
+// fp16 GELU of a block with groups.  The kernels of a handful of pixels
+// (cf_slice.hip, cf_small.hip) work in fp32, and so do the groups up to 1024
+// pixels, where it costs a launch of latencies little: 4 images of 14 x 14 at
+// C = 256 18.2 us with the packed polynomial, 18.4 with fp32; 49 pixels 13.7 and
+// 13.9, at C = 512 23.0 and 22.9.  Above, the polynomial of the larger batches:
+// 16 such images 26.6 and 27.5 us, 64 of 7 x 7 at C = 512 64.3 and 67.2.
+int ffn_group_cfg(const Shape &whole) {
+    return (int64_t)whole.N * whole.H * whole.W <= 1024 ? CFG_FFN_F32 : CFG_FFN;
 }
 
 hipError_t launch_ffn_block(const void *x, void *y, const BlockW &w, const Shape &s, int groups, float *part,

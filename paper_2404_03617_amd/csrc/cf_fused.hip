@@ -112,7 +112,7 @@ hipError_t launch_fused_block(const void *x, void *y, const BlockW &w, const Sha
     a.P = (uint32_t)((int64_t)s.N * s.H * s.W);
     hipError_t e;
     bool done = false;
-    if (groups > 1 && s.cfg == CFG_FFN) {
+    if (groups > 1 && (s.cfg == CFG_FFN || s.cfg == CFG_FFN_F32)) {
         if ((e = launch_ffn_block(x, y, w, s, groups, partial, st)) != hipSuccess)
             return e;
         done = true;

@@ -56,6 +56,7 @@ enum {
     CFG_TILE = 3,        // N*H*W <= 64: the tile kernels where the default is the slice kernel
     CFG_COUNT = 4,
     CFG_FFN = 8,         // the two-launch block split into hidden groups (never autotuned: needs a workspace)
+    CFG_FFN_F32 = 10,    // the same, fp16 with the fp32 GELU
     CFG_SINGLE = 9       // the single-launch kernel, for a part of a batch that takes it as a whole
 };
 // Whether configuration cfg applies to shape s.
@@ -91,11 +92,13 @@ hipError_t launch_slice(const void *x, void *y, const BlockW &w, const Shape &s,
 // groups > 1: partial holds fp32 [groups][N*H*W][C]; the caller adds the
 // groups, b2 and x.  ffn_groups: how many a shape is worth, 1 for none;
 // ffn_fitting_groups: those of `whole` whose partials of `one` bytes fit
-// `bytes`.  launch_ffn_block takes only a count that leaves no group empty, as
+// `bytes`; ffn_group_cfg: CFG_FFN or CFG_FFN_F32, whichever the groups of
+// `whole` run as.  launch_ffn_block takes only a count that leaves no group empty, as
 // both return.
 bool ffn_applies(const Shape &s);
 int ffn_groups(const Shape &s);
 int ffn_fitting_groups(const Shape &whole, size_t one, size_t bytes);
+int ffn_group_cfg(const Shape &whole);
 hipError_t launch_ffn_block(const void *x, void *y, const BlockW &w, const Shape &s, int groups, float *partial,
                             hipStream_t st);
 
