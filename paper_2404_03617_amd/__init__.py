@@ -12,6 +12,7 @@ I/O dtype and optional fp32 s0,b0 [C], s1,b1 [E*C], s2,b2 [C].
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import importlib.util
 import os
@@ -319,11 +320,11 @@ def _out(x: torch.Tensor, out, shape=None):
     return out
 
 
-def _workspace(x: torch.Tensor, ws, need: int):
+def _workspace(x: torch.Tensor, ws, need: int, stream):
     """The caller's workspace (uint8, on x's device, at least `need` bytes) or a
-    fresh one."""
+    fresh one for a call on `stream`."""
     if ws is None:
-        return torch.empty(need, dtype=torch.uint8, device=x.device) if need else None
+        return _scratch(x, need, stream)
     if not isinstance(ws, torch.Tensor) or ws.dtype != torch.uint8 or not ws.is_contiguous():
         raise ValueError("ws must be a contiguous uint8 tensor")
     if ws.device != x.device:
@@ -350,15 +351,26 @@ def _split_bytes(x: torch.Tensor, hidden: int) -> int:
     return min(SPLIT_BYTES, 64 * pixels * C * 4)
 
 
+def _allocating_for(x: torch.Tensor, stream):
+    """A context in which torch allocates from the pool of `stream`, any object
+    with a cuda_stream handle (None: the current stream's, as without)."""
+    if stream is None:
+        return contextlib.nullcontext()
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=x.device)
+    return torch.cuda.stream(stream)
+
+
 def _scratch(x: torch.Tensor, nbytes: int, stream):
-    """`nbytes` of device memory for one call (None for 0), safe to drop while
-    the call still runs on `stream`."""
+    """`nbytes` of device memory for one call on `stream` (None for 0), from
+    that stream's own pool: whoever used the block before or gets it after the
+    call ran or will run on the same stream.  (From the current stream's pool
+    it could be a block that the current stream freed with work on it still
+    queued, which nothing orders before the call.)"""
     if not nbytes:
         return None
-    ws = torch.empty(nbytes, dtype=torch.uint8, device=x.device)
-    if stream is not None:
-        ws.record_stream(stream)
-    return ws
+    with _allocating_for(x, stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=x.device)
 
 
 def _prepare_block(x: torch.Tensor, p: dict, act: str, out):
@@ -439,7 +451,7 @@ def stage_forward(x: torch.Tensor, blocks: list, act: str = "gelu", out=None, ws
     y, arr, (N, H, W, C, E, k) = _prepare_stage(x, blocks, out)
     L = lib()
     need = L.cf_stage_workspace_bytes(len(blocks), N, H, W, C, DTYPES[x.dtype])
-    ws = _scratch(x, need + _split_bytes(x, E * C), stream) if ws is None else _workspace(x, ws, need)
+    ws = _scratch(x, need + _split_bytes(x, E * C), stream) if ws is None else _workspace(x, ws, need, stream)
     _check(L.cf_stage_forward(_ptr(x), _ptr(y), _ptr(ws), 0 if ws is None else ws.numel(),
                               arr, len(blocks), N, H, W, C, E, k, DTYPES[x.dtype], ACTS[act],
                               _stream(stream)))
@@ -458,7 +470,7 @@ def stage_forward_microbatch(x: torch.Tensor, blocks: list, act: str = "gelu", m
     y, arr, (N, H, W, C, E, k) = _prepare_stage(x, blocks, out)
     L = lib()
     need = L.cf_stage_microbatch_workspace_bytes(len(blocks), N, H, W, C, micro_batch, DTYPES[x.dtype])
-    ws = _scratch(x, need + _split_bytes(x, E * C), stream) if ws is None else _workspace(x, ws, need)
+    ws = _scratch(x, need + _split_bytes(x, E * C), stream) if ws is None else _workspace(x, ws, need, stream)
     _check(L.cf_stage_forward_microbatch(_ptr(x), _ptr(y), _ptr(ws), 0 if ws is None else ws.numel(), arr,
                                          len(blocks), N, H, W, C, E, k, micro_batch, DTYPES[x.dtype], ACTS[act],
                                          _stream(stream)))
@@ -500,7 +512,7 @@ def block_forward_unfused(x: torch.Tensor, p: dict, act: str = "gelu", out=None,
     """Layer-by-layer block: depth-wise, expand GEMM, project GEMM (3 launches)."""
     y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out)
     L = lib()
-    ws = _workspace(x, ws, L.cf_unfused_workspace_bytes(N, H, W, C, E, DTYPES[x.dtype]))
+    ws = _workspace(x, ws, L.cf_unfused_workspace_bytes(N, H, W, C, E, DTYPES[x.dtype]), stream)
     _check(L.cf_block_forward_unfused(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), ctypes.byref(bp),
                                       N, H, W, C, E, k, DTYPES[x.dtype], ACTS[act], _stream(stream)))
     return y
@@ -516,7 +528,7 @@ def block_forward_split(x: torch.Tensor, p: dict, act: str = "gelu", groups: int
     """Fused block with hidden channels split over `groups` workgroups per tile."""
     y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out)
     L = lib()
-    ws = _workspace(x, ws, L.cf_split_workspace_bytes(N, H, W, C, E, groups))
+    ws = _workspace(x, ws, L.cf_split_workspace_bytes(N, H, W, C, E, groups), stream)
     _check(L.cf_block_forward_split(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), ctypes.byref(bp),
                                     N, H, W, C, E, k, groups, DTYPES[x.dtype], ACTS[act],
                                     _stream(stream)))
@@ -810,7 +822,7 @@ def mbconv_forward(x: torch.Tensor, p: dict, out=None, ws=None, launch: str = "c
     if ws is None:
         ws = _scratch(x, max(1, mbconv_workspace_bytes(N, H, W, C, E, R, x.dtype)), stream)
     else:
-        _workspace(x, ws, 0)
+        _workspace(x, ws, 0, stream)
     _check(lib().cf_mbconv_forward(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), mp, N, H, W, C, E,
                                    R, k, DTYPES[x.dtype], LAUNCHES[launch], _stream(stream)))
     return y
@@ -830,7 +842,7 @@ def mbconv_s2_forward(x: torch.Tensor, p: dict, out=None, ws=None, launch: str =
     if ws is None:
         ws = _scratch(x, max(1, mbconv_s2_workspace_bytes(N, H, W, C, E, R, K, x.dtype)), stream)
     else:
-        _workspace(x, ws, 0)
+        _workspace(x, ws, 0, stream)
     _check(lib().cf_mbconv_s2_forward(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), mp, N, H, W, C, E,
                                       R, K, k, DTYPES[x.dtype], LAUNCHES[launch], _stream(stream)))
     return y

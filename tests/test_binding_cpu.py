@@ -215,3 +215,34 @@ def test_layout_conversions_on_known_values():
     w = torch.arange(4 * 6 * 2 * 2).reshape(4, 6, 2, 2)
     dn = cf.down_weight_from_conv2d(w)
     assert dn.shape == (4, 2, 2, 6) and dn[3, 1, 0, 5] == w[3, 5, 1, 0]
+
+
+@pytest.mark.parametrize("through", ["_scratch", "_workspace"])
+def test_scratch_is_allocated_in_the_pool_of_the_call_s_stream(monkeypatch, through):
+    """A block of the current stream's pool may have been freed with that
+    stream's work on it still queued; nothing orders a call on another stream
+    behind it.  So the allocation itself happens on the call's stream."""
+    class Handle:
+        cuda_stream = 7
+
+    seen, on = [], [None]
+
+    class On:
+        def __init__(self, stream):
+            self.stream = stream
+
+        def __enter__(self):
+            on[0] = self.stream
+
+        def __exit__(self, *a):
+            on[0] = None
+
+    empty = torch.empty
+    monkeypatch.setattr(torch.cuda, "stream", On)
+    monkeypatch.setattr(torch.cuda, "ExternalStream", lambda handle, device=None: ("external", handle))
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: (seen.append(on[0]), empty(*a, **k))[1])
+    x = torch.zeros(1)
+    for stream, want in ((None, None), (Handle(), ("external", 7))):
+        ws = cf._scratch(x, 64, stream) if through == "_scratch" else cf._workspace(x, None, 64, stream)
+        assert ws.numel() == 64 and seen.pop() == want and not seen
+    assert cf._scratch(x, 0, Handle()) is None and not seen

@@ -1,0 +1,59 @@
+"""Calls on a stream of the caller's: their scratch memory comes from that
+stream's pool, and the outputs are those of the default stream."""
+import sys
+
+import pytest
+import torch
+
+import paper_2404_03617_amd as cf
+from paper_2404_03617_amd import synth
+
+from _util import make_block, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+def calls():
+    """name -> call of the stream"""
+    x, p = make_block(95, 4, 14, 14, 256, 4, 3)
+    x, p, q = x.cuda(), to_dev(p), to_dev(make_block(95, 4, 14, 14, 256, 4, 3, layer=1)[1])
+    x5, p5 = make_block(95, 1, 7, 7, 512, 4, 3, "bf16")
+    x5, p5 = x5.cuda(), to_dev(p5)
+    xm = synth.activations(95, 2, 12, 10, 64).cuda()
+    m, m2 = (to_dev(synth.mbconv_params(95, i, 64, 4, 16)) for i in range(2))
+    m2 = dict(m2, w2=m2["w2"][:64].contiguous())
+    y, y5, ym = torch.empty_like(x), torch.empty_like(x5), torch.empty_like(xm)
+    yh = torch.empty(2, 6, 5, 64, dtype=xm.dtype, device="cuda")
+    return {
+        "block c256": lambda s: cf.block_forward(x, p, out=y, stream=s),
+        "block c512": lambda s: cf.block_forward(x5, p5, out=y5, stream=s),
+        "stage": lambda s: cf.stage_forward(x, [p, q], out=y, stream=s),
+        "microbatch": lambda s: cf.stage_forward_microbatch(x, [p, q], micro_batch=3, out=y, stream=s),
+        "unfused": lambda s: cf.block_forward_unfused(x, p, out=y, stream=s),
+        "split": lambda s: cf.block_forward_split(x5, p5, groups=4, out=y5, stream=s),
+        "mbconv": lambda s: cf.mbconv_forward(xm, m, out=ym, stream=s),
+        "mbconv_s2": lambda s: cf.mbconv_s2_forward(xm, m2, out=yh, stream=s),
+    }
+
+
+@pytest.mark.parametrize("name", ["block c256", "block c512", "stage", "microbatch", "unfused", "split", "mbconv",
+                                  "mbconv_s2"])
+def test_call_on_a_side_stream(name, monkeypatch):
+    say("side stream", name)
+    call = calls()[name]
+    want = call(None).clone()
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    empty, at = torch.empty, []
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: (at.append(torch.cuda.current_stream()), empty(*a, **k))[1])
+    got = call(side)
+    monkeypatch.undo()
+    side.synchronize()
+    assert torch.equal(got, want)
+    assert at and all(s == side for s in at), at
+    assert torch.cuda.current_stream() == torch.cuda.default_stream()
