@@ -136,11 +136,11 @@ def _shape(p, key, dims):
     return sh if sh is not None and len(sh) == dims else None
 
 
-def _y_fast(x, out, shape):
+def _y_fast(x, out, shape, stream):
     """(y, its address) for a call whose x is checked; None where out is not as
     it should be."""
     if out is None:
-        y = torch.empty(shape, dtype=x.dtype, device=x.device)
+        y = _new(x, shape, stream)
         return y, y.data_ptr()
     ptr = _args.like(x, out, shape)
     return None if ptr is None else (out, ptr)
@@ -310,10 +310,10 @@ def _block_struct(x: torch.Tensor, p: dict, keep: list) -> _BlockParams:
     return _BlockParams(**vals)
 
 
-def _out(x: torch.Tensor, out, shape=None):
+def _out(x: torch.Tensor, out, stream, shape=None):
     shape = tuple(x.shape) if shape is None else tuple(shape)
     if out is None:
-        return torch.empty(shape, dtype=x.dtype, device=x.device)
+        return _new(x, shape, stream)
     if _args is not None and _args.like(x, out, shape) is not None:
         return out
     _check_tensor("out", out, shape, x.dtype, x.device)
@@ -361,6 +361,17 @@ def _allocating_for(x: torch.Tensor, stream):
     return torch.cuda.stream(stream)
 
 
+def _new(x: torch.Tensor, shape, stream):
+    """A new output of a call on `stream`: from that stream's pool, as scratch
+    is, and not handed out again before the current stream, on which the caller
+    goes on, has done what it has queued when the output is dropped."""
+    with _allocating_for(x, stream):
+        y = torch.empty(shape, dtype=x.dtype, device=x.device)
+    if stream is not None:
+        y.record_stream(torch.cuda.current_stream(x.device))
+    return y
+
+
 def _scratch(x: torch.Tensor, nbytes: int, stream):
     """`nbytes` of device memory for one call on `stream` (None for 0), from
     that stream's own pool: whoever used the block before or gets it after the
@@ -373,7 +384,7 @@ def _scratch(x: torch.Tensor, nbytes: int, stream):
         return torch.empty(nbytes, dtype=torch.uint8, device=x.device)
 
 
-def _prepare_block(x: torch.Tensor, p: dict, act: str, out):
+def _prepare_block(x: torch.Tensor, p: dict, act: str, out, stream):
     """Every check of a block call, in an order that needs no GPU: shapes and
     dtypes first, then devices.  Returns (y, struct, keep, dims)."""
     if act not in ACTS:
@@ -381,7 +392,7 @@ def _prepare_block(x: torch.Tensor, p: dict, act: str, out):
     keep = []
     bp = _block_struct(x, p, keep)
     _check_device(x)
-    y = _out(x, out)
+    y = _out(x, out, stream)
     return y, bp, keep, _block_shape(x, p)
 
 
@@ -390,11 +401,11 @@ def block_forward(x: torch.Tensor, p: dict, act: str = "gelu", out: torch.Tensor
     """Fused ConvFirst block: y = x + FFN(dwconv(x)).  A wide block over few
     pixels takes scratch memory for its hidden split from torch's allocator."""
     f = _block_fast(x, p) if act in ACTS else None
-    yf = None if f is None else _y_fast(x, out, f[:4])
+    yf = None if f is None else _y_fast(x, out, f[:4], stream)
     if yf is not None:
         (N, H, W, C, dt, xp, E, k, bp), (y, yp) = f, yf
     else:
-        y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out)
+        y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out, stream)
         dt, xp, yp, bp = DTYPES[x.dtype], x.data_ptr(), y.data_ptr(), ctypes.byref(bp)
     ws = _scratch(x, _split_bytes(x, E * C), stream)
     if ws is not None:  # the hidden split beats every configuration the tuner knows
@@ -410,7 +421,7 @@ def block_autotune(x: torch.Tensor, p: dict, act: str = "gelu", out: torch.Tenso
     """Time every kernel configuration that applies to this block shape, cache
     the fastest for later block_forward calls (those with a hidden split keep
     it), return the block's output."""
-    y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out)
+    y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out, stream)
     _check(lib().cf_block_autotune(_ptr(x), _ptr(y), ctypes.byref(bp), N, H, W, C, E, k,
                                    DTYPES[x.dtype], ACTS[act], _stream(stream)))
     if _split_bytes(x, E * C):
@@ -424,12 +435,12 @@ def block_tuned_config(x_shape, C: int, E: int, k: int, dtype=torch.float16, act
     return lib().cf_block_tuned_config(N, H, W, C, E, k, DTYPES[dtype], ACTS[act])
 
 
-def _prepare_stage(x: torch.Tensor, blocks: list, out):
+def _prepare_stage(x: torch.Tensor, blocks: list, out, stream):
     """The checked arguments of a stage: (y, the blocks' structs, sizes)."""
     fast = [_block_fast(x, b) for b in blocks]
     if None not in fast and len({f[:8] for f in fast}) == 1:
         N, H, W, C, _, _, E, k, _ = fast[0]
-        yf = _y_fast(x, out, (N, H, W, C))
+        yf = _y_fast(x, out, (N, H, W, C), stream)
         if yf is not None:
             return yf[0], b"".join(f[8] for f in fast), (N, H, W, C, E, k)
     keep = []
@@ -438,7 +449,7 @@ def _prepare_stage(x: torch.Tensor, blocks: list, out):
     if len(dims) != 1:
         raise ValueError("every block of a stage must have the same shape")
     _check_device(x)
-    return _out(x, out), (_BlockParams * len(blocks))(*structs), dims.pop()
+    return _out(x, out, stream), (_BlockParams * len(blocks))(*structs), dims.pop()
 
 
 def stage_forward(x: torch.Tensor, blocks: list, act: str = "gelu", out=None, ws=None,
@@ -448,7 +459,7 @@ def stage_forward(x: torch.Tensor, blocks: list, act: str = "gelu", out=None, ws
         raise ValueError("a stage needs at least one block")
     if act not in ACTS:
         raise ValueError("act must be one of %s" % sorted(ACTS))
-    y, arr, (N, H, W, C, E, k) = _prepare_stage(x, blocks, out)
+    y, arr, (N, H, W, C, E, k) = _prepare_stage(x, blocks, out, stream)
     L = lib()
     need = L.cf_stage_workspace_bytes(len(blocks), N, H, W, C, DTYPES[x.dtype])
     ws = _scratch(x, need + _split_bytes(x, E * C), stream) if ws is None else _workspace(x, ws, need, stream)
@@ -467,7 +478,7 @@ def stage_forward_microbatch(x: torch.Tensor, blocks: list, act: str = "gelu", m
         raise ValueError("a stage needs at least one block")
     if act not in ACTS:
         raise ValueError("act must be one of %s" % sorted(ACTS))
-    y, arr, (N, H, W, C, E, k) = _prepare_stage(x, blocks, out)
+    y, arr, (N, H, W, C, E, k) = _prepare_stage(x, blocks, out, stream)
     L = lib()
     need = L.cf_stage_microbatch_workspace_bytes(len(blocks), N, H, W, C, micro_batch, DTYPES[x.dtype])
     ws = _scratch(x, need + _split_bytes(x, E * C), stream) if ws is None else _workspace(x, ws, need, stream)
@@ -484,7 +495,7 @@ def downsample_forward(x: torch.Tensor, p: dict, out=None, stream=None) -> torch
     if wd is not None:
         N, H, W, Cin, dt, xp = d
         dp = _args.collect(_DOWN_SPEC, x, p, (wd[0], 2, Cin))
-        yf = None if dp is None else _y_fast(x, out, (N, H // 2, W // 2, wd[0]))
+        yf = None if dp is None else _y_fast(x, out, (N, H // 2, W // 2, wd[0]), stream)
         if yf is not None:
             _check(lib().cf_downsample_forward(xp, yf[1], dp, N, H, W, Cin, wd[0], dt, _stream(stream)))
             return yf[0]
@@ -498,7 +509,7 @@ def downsample_forward(x: torch.Tensor, p: dict, out=None, stream=None) -> torch
         if p.get(key) is not None:
             _check_tensor(key, p[key], (Cout,), torch.float32, x.device)
     _check_device(x)
-    y = _out(x, out, (N, H // 2, W // 2, Cout))
+    y = _out(x, out, stream, (N, H // 2, W // 2, Cout))
     dp = _DownParams(w=wd.data_ptr(),
                      scale=None if p.get("sd") is None else p["sd"].data_ptr(),
                      bias=None if p.get("bd") is None else p["bd"].data_ptr())
@@ -510,7 +521,7 @@ def downsample_forward(x: torch.Tensor, p: dict, out=None, stream=None) -> torch
 def block_forward_unfused(x: torch.Tensor, p: dict, act: str = "gelu", out=None, ws=None,
                           stream=None) -> torch.Tensor:
     """Layer-by-layer block: depth-wise, expand GEMM, project GEMM (3 launches)."""
-    y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out)
+    y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out, stream)
     L = lib()
     ws = _workspace(x, ws, L.cf_unfused_workspace_bytes(N, H, W, C, E, DTYPES[x.dtype]), stream)
     _check(L.cf_block_forward_unfused(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), ctypes.byref(bp),
@@ -526,7 +537,7 @@ def split_workspace_bytes(x_shape, C: int, E: int, groups: int = 0) -> int:
 def block_forward_split(x: torch.Tensor, p: dict, act: str = "gelu", groups: int = 0, out=None,
                         ws=None, stream=None) -> torch.Tensor:
     """Fused block with hidden channels split over `groups` workgroups per tile."""
-    y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out)
+    y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out, stream)
     L = lib()
     ws = _workspace(x, ws, L.cf_split_workspace_bytes(N, H, W, C, E, groups), stream)
     _check(L.cf_block_forward_split(_ptr(x), _ptr(y), _ptr(ws), ws.numel(), ctypes.byref(bp),
@@ -552,7 +563,7 @@ def gblock_forward(x: torch.Tensor, p: dict, act: str = "relu", out=None, stream
         raise ValueError("act must be one of %s" % sorted(ACTS))
     d = None if _args is None else _args.tensor4(x)
     f = None if d is None else _gblock_fast(x, p, d[3])
-    yf = None if f is None else _y_fast(x, out, d[:4])
+    yf = None if f is None else _y_fast(x, out, d[:4], stream)
     if yf is not None:
         (N, H, W, C, dt, xp), (E, k, gp) = d, f
         _check(lib().cf_gblock_forward(xp, yf[1], gp, N, H, W, C, E, k, dt, ACTS[act], _stream(stream)))
@@ -578,7 +589,7 @@ def gblock_forward(x: torch.Tensor, p: dict, act: str = "relu", out=None, stream
         vals[_GFIELDS[key]] = None if t is None else t.data_ptr()
     gp = _GBlockParams(**vals)
     _check_device(x)
-    y = _out(x, out)
+    y = _out(x, out, stream)
     _check(lib().cf_gblock_forward(_ptr(x), _ptr(y), ctypes.byref(gp), N, H, W, C, EC // C, k,
                                    DTYPES[x.dtype], ACTS[act], _stream(stream)))
     return y
@@ -612,7 +623,7 @@ def convfirst_s2_forward(x: torch.Tensor, p: dict, act: str = "relu", out=None, 
         N, H, W, C, dt, xp = d
         k, R, K = gw[0], w1[0], w2[0]
         gp = _args.collect(_CFS2_SPEC, x, p, (k, C, R, GROUP_WIDTH, 2 * C, K))
-        yf = None if gp is None else _y_fast(x, out, (N, (H + 1) // 2, (W + 1) // 2, K))
+        yf = None if gp is None else _y_fast(x, out, (N, (H + 1) // 2, (W + 1) // 2, K), stream)
         if yf is not None:
             _check(lib().cf_convfirst_s2_forward(xp, yf[1], gp, N, H, W, C, R, K, k, dt, ACTS[act], _stream(stream)))
             return yf[0]
@@ -638,7 +649,7 @@ def convfirst_s2_forward(x: torch.Tensor, p: dict, act: str = "relu", out=None, 
         vals[_GFIELDS[key]] = None if t is None else t.data_ptr()
     gp = _GBlockParams(**vals)
     _check_device(x)
-    y = _out(x, out, (N, (H + 1) // 2, (W + 1) // 2, K))
+    y = _out(x, out, stream, (N, (H + 1) // 2, (W + 1) // 2, K))
     _check(lib().cf_convfirst_s2_forward(_ptr(x), _ptr(y), ctypes.byref(gp), N, H, W, C, R, K, k,
                                          DTYPES[x.dtype], ACTS[act], _stream(stream)))
     return y
@@ -679,7 +690,7 @@ def stem_forward(x: torch.Tensor, stem: dict, out=None, stream=None) -> torch.Te
     C = int(stem["sw"].shape[0])
     sp = _stem_struct(x, stem, C)
     _check_device(x)
-    y = _out(x, out, (N, (H + 1) // 2, (W + 1) // 2, C))
+    y = _out(x, out, stream, (N, (H + 1) // 2, (W + 1) // 2, C))
     _check(lib().cf_stem_forward(_ptr(x), _ptr(y), ctypes.byref(sp), N, H, W, C, DTYPES[x.dtype], _stream(stream)))
     return y
 
@@ -697,7 +708,7 @@ def stem_gblock_forward(x: torch.Tensor, stem: dict, p: dict, act: str = "relu",
         (N, H, W, _, dt, xp), C = d, sw[0]
         sp = _args.collect(_STEM_SPEC, x, stem, (C, 3))
         f = None if sp is None or not C else _gblock_fast(x, p, C)
-        yf = None if f is None else _y_fast(x, out, (N, (H + 1) // 2, (W + 1) // 2, C))
+        yf = None if f is None else _y_fast(x, out, (N, (H + 1) // 2, (W + 1) // 2, C), stream)
         if yf is not None:
             E, k, gp = f
             _check(lib().cf_stem_gblock_forward(xp, yf[1], sp, gp, N, H, W, C, E, k, dt, ACTS[act], _stream(stream)))
@@ -726,7 +737,7 @@ def stem_gblock_forward(x: torch.Tensor, stem: dict, p: dict, act: str = "relu",
         vals[_GFIELDS[key]] = _ptr_val(t)
     gp = _GBlockParams(**vals)
     _check_device(x)
-    y = _out(x, out, (N, (H + 1) // 2, (W + 1) // 2, C))
+    y = _out(x, out, stream, (N, (H + 1) // 2, (W + 1) // 2, C))
     _check(lib().cf_stem_gblock_forward(_ptr(x), _ptr(y), ctypes.byref(sp), ctypes.byref(gp), N, H, W, C, EC // C, k,
                                         DTYPES[x.dtype], ACTS[act], _stream(stream)))
     return y
@@ -818,7 +829,7 @@ def mbconv_forward(x: torch.Tensor, p: dict, out=None, ws=None, launch: str = "c
     mbconv_workspace_bytes(); a smaller one runs fewer images at a time.
     launch: "cooperative" and "exclusive" launch alike (see the C header)."""
     (N, H, W, C, E, R, _, k), mp, keep = _mbconv_args(x, p, launch, False)
-    y = _out(x, out)
+    y = _out(x, out, stream)
     if ws is None:
         ws = _scratch(x, max(1, mbconv_workspace_bytes(N, H, W, C, E, R, x.dtype)), stream)
     else:
@@ -838,7 +849,7 @@ def mbconv_s2_forward(x: torch.Tensor, p: dict, out=None, ws=None, launch: str =
     [N, ceil(H/2), ceil(W/2), K] and must not overlap x.  ws as for
     mbconv_forward, sized by mbconv_s2_workspace_bytes()."""
     (N, H, W, C, E, R, K, k), mp, keep = _mbconv_args(x, p, launch, True)
-    y = _out(x, out, (N, (H + 1) // 2, (W + 1) // 2, K))
+    y = _out(x, out, stream, (N, (H + 1) // 2, (W + 1) // 2, K))
     if ws is None:
         ws = _scratch(x, max(1, mbconv_s2_workspace_bytes(N, H, W, C, E, R, K, x.dtype)), stream)
     else:
@@ -854,7 +865,7 @@ def block_forward_split_noalloc(x: torch.Tensor, p: dict, act: str = "gelu", gro
     partials in a static device array (16 MiB per GPU), so with `out` given the
     call allocates nothing.  Calls that overlap on one GPU race (see the C
     header)."""
-    y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out)
+    y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out, stream)
     _check(lib().cf_block_forward_split_noalloc(_ptr(x), _ptr(y), ctypes.byref(bp), N, H, W, C, E, k, groups,
                                                 DTYPES[x.dtype], ACTS[act], _stream(stream)))
     return y

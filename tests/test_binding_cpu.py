@@ -217,8 +217,8 @@ def test_layout_conversions_on_known_values():
     assert dn.shape == (4, 2, 2, 6) and dn[3, 1, 0, 5] == w[3, 5, 1, 0]
 
 
-@pytest.mark.parametrize("through", ["_scratch", "_workspace"])
-def test_scratch_is_allocated_in_the_pool_of_the_call_s_stream(monkeypatch, through):
+@pytest.mark.parametrize("through", ["_scratch", "_workspace", "_out"])
+def test_memory_is_allocated_in_the_pool_of_the_call_s_stream(monkeypatch, through):
     """A block of the current stream's pool may have been freed with that
     stream's work on it still queued; nothing orders a call on another stream
     behind it.  So the allocation itself happens on the call's stream."""
@@ -241,8 +241,14 @@ def test_scratch_is_allocated_in_the_pool_of_the_call_s_stream(monkeypatch, thro
     monkeypatch.setattr(torch.cuda, "stream", On)
     monkeypatch.setattr(torch.cuda, "ExternalStream", lambda handle, device=None: ("external", handle))
     monkeypatch.setattr(torch, "empty", lambda *a, **k: (seen.append(on[0]), empty(*a, **k))[1])
+    held = []
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: "current")
+    monkeypatch.setattr(torch.Tensor, "record_stream", lambda self, s: held.append(s))
     x = torch.zeros(1)
     for stream, want in ((None, None), (Handle(), ("external", 7))):
-        ws = cf._scratch(x, 64, stream) if through == "_scratch" else cf._workspace(x, None, 64, stream)
+        ws = (cf._scratch(x, 64, stream) if through == "_scratch" else
+              cf._workspace(x, None, 64, stream) if through == "_workspace" else cf._out(x, None, stream, (64,)))
+        if through == "_out":
+            assert held == ([] if stream is None else ["current"])
         assert ws.numel() == 64 and seen.pop() == want and not seen
     assert cf._scratch(x, 0, Handle()) is None and not seen

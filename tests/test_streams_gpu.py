@@ -1,5 +1,5 @@
-"""Calls on a stream of the caller's: their scratch memory comes from that
-stream's pool, and the outputs are those of the default stream."""
+"""Calls on a stream of the caller's: their scratch memory and new outputs come
+from that stream's pool, and the outputs are those of the default stream."""
 import sys
 
 import pytest
@@ -18,8 +18,8 @@ def say(*a):
     sys.stdout.flush()
 
 
-def calls():
-    """name -> call of the stream"""
+def calls(out):
+    """name -> call of the stream, with an output of the caller's or without"""
     x, p = make_block(95, 4, 14, 14, 256, 4, 3)
     x, p, q = x.cuda(), to_dev(p), to_dev(make_block(95, 4, 14, 14, 256, 4, 3, layer=1)[1])
     x5, p5 = make_block(95, 1, 7, 7, 512, 4, 3, "bf16")
@@ -27,9 +27,19 @@ def calls():
     xm = synth.activations(95, 2, 12, 10, 64).cuda()
     m, m2 = (to_dev(synth.mbconv_params(95, i, 64, 4, 16)) for i in range(2))
     m2 = dict(m2, w2=m2["w2"][:64].contiguous())
+    r, g = to_dev(make_block(95, 4, 7, 7, 512, 4, 3)[1]), to_dev(synth.gblock_params(95, 0, 64, 4, 3))
     y, y5, ym = torch.empty_like(x), torch.empty_like(x5), torch.empty_like(xm)
     yh = torch.empty(2, 6, 5, 64, dtype=xm.dtype, device="cuda")
+    if not out:
+        y = y5 = ym = yh = None
+    d = {"wd": torch.randn(512, 2, 2, 256).half().cuda() / 32, "sd": None, "bd": None}
+    more = {} if out else {
+        "down": lambda s: cf.downsample_forward(x, d, stream=s),
+        "stack": lambda s: cf.stack_forward(x, [("block", p), ("down", d), ("block", r)], stream=s),
+        "gblock": lambda s: cf.gblock_forward(xm, g, stream=s),
+    }
     return {
+        **more,
         "block c256": lambda s: cf.block_forward(x, p, out=y, stream=s),
         "block c512": lambda s: cf.block_forward(x5, p5, out=y5, stream=s),
         "stage": lambda s: cf.stage_forward(x, [p, q], out=y, stream=s),
@@ -41,11 +51,14 @@ def calls():
     }
 
 
-@pytest.mark.parametrize("name", ["block c256", "block c512", "stage", "microbatch", "unfused", "split", "mbconv",
-                                  "mbconv_s2"])
-def test_call_on_a_side_stream(name, monkeypatch):
-    say("side stream", name)
-    call = calls()[name]
+SCRATCH = ["block c256", "block c512", "stage", "microbatch", "unfused", "split", "mbconv", "mbconv_s2"]
+
+
+@pytest.mark.parametrize("name,out", [(n, True) for n in SCRATCH] +
+                         [(n, False) for n in SCRATCH + ["down", "stack", "gblock"]])
+def test_call_on_a_side_stream(name, out, monkeypatch):
+    say("side stream", name, out)
+    call = calls(out)[name]
     want = call(None).clone()
     side = torch.cuda.Stream()
     torch.cuda.synchronize()
@@ -53,7 +66,7 @@ def test_call_on_a_side_stream(name, monkeypatch):
     monkeypatch.setattr(torch, "empty", lambda *a, **k: (at.append(torch.cuda.current_stream()), empty(*a, **k))[1])
     got = call(side)
     monkeypatch.undo()
-    side.synchronize()
+    torch.cuda.current_stream().wait_stream(side)
     assert torch.equal(got, want)
     assert at and all(s == side for s in at), at
     assert torch.cuda.current_stream() == torch.cuda.default_stream()
