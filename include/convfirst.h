@@ -116,7 +116,8 @@ cf_status cf_block_forward(const void *x, void *y, const cf_block_params *p,
  * kernels, deterministic.
  * Otherwise, at C = 256 and 512 over few pixels, each block splits its hidden
  * layer over as many groups of workgroups as the room behind the minimum holds
- * (4*N*H*W*C bytes a group; a larger ws than recommended is used as well).
+ * (4*N*H*W*C bytes a group; a larger ws than recommended is used as well);
+ * at C = 512 fp16 and E > 7 over as many as the recommended room holds.
  * With any number of groups results are identical up to fp32 summation order;
  * without, a C = 512 or C = 256 fp16 block above 64 pixels takes the packed
  * GELU polynomial (with groups, only above 1024 pixels) and for k >= 5 sums the

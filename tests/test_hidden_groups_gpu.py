@@ -111,3 +111,21 @@ def test_fp16_gelu_over_few_pixels_is_that_of_fp32(case):
     err = float((y - ref).norm() / ref.norm())
     print("  relative error %.2e" % err, flush=True)
     assert err < 2.0 ** -11
+
+
+@pytest.mark.parametrize("N", [2, 24])
+def test_stage_too_wide_for_the_two_launch_block_keeps_its_groups(N):
+    """C = 512, E = 8 in fp16: the hidden layer is split over four groups
+    (N = 2: the small-batch kernel, N = 24: the streaming one) whose partials
+    the workspace of the recommended size holds; the run without room for them
+    gives the same up to the order of the sums."""
+    H, W, C, E, k = 7, 7, 512, 8, 3
+    x, p = make_block(96, N, H, W, C, E, k, "f16")
+    ref = oracle_block(x, p)
+    say("wide groups", N)
+    xd, pd = x.cuda(), to_dev(p)
+    y, written = run(xd, pd, cf.lib().cf_stage_workspace_bytes(1, N, H, W, C, cf.DTYPES[x.dtype]))
+    assert written == 4
+    assert_close(y.cpu(), ref, what="E = 8 stage, groups", diag=DIAG_F16)
+    y, _ = run(xd, pd, 0)
+    assert_close(y.cpu(), ref, what="E = 8 stage, no room", diag=DIAG_F16)
