@@ -299,11 +299,16 @@ bool ffn_applies(const Shape &s) {
 // captured graph, groups 1 / 2 / 4 / 8 / 16 / 32: 4 images of 14 x 14 at
 // C = 256 fp16 39.0 / 24.7 / 22.4 / 22.4 / 29.0 / - us; one image of 7 x 7 at
 // C = 512 bf16 64.8 / 60.7 / 37.2 / 28.3 / 24.8 / 24.3 us.  C = 128 gains
-// nothing (20.4 / 19.9 / 21.1 us for 4 images of 28 x 28 in bf16).
+// nothing (20.4 / 19.9 / 21.1 us for 4 images of 28 x 28 in bf16), nor do the
+// four chunks of C = 256, E = 1, whose groups are all prologue and reduction: k = 3
+// fp16, with groups / without (up to 64 pixels the slice kernel) 13.4 / 12.2 us
+// for 16 pixels, 14.3 / 16.5 for 49, 14.4 / 12.8 for 196, 22.6 / 16.8 for 3920.
 int ffn_groups(const Shape &s) {
     if (!ffn_applies(s) || s.C == 128)
         return 1;
     const int64_t P = (int64_t)s.N * s.H * s.W;
+    if (s.C == 256 && s.E == 1 && (P <= 16 || P > 64))
+        return 1;
     const int px = s.C == 256 ? 32 : 64;
     const int64_t tiles = (P + px - 1) / px, chunks = s.E * s.C / ffn::chunk(s.C);
     const int64_t most = s.C == 512 ? chunks / 2 : chunks;

@@ -113,6 +113,20 @@ def test_fp16_gelu_over_few_pixels_is_that_of_fp32(case):
     assert err < 2.0 ** -11
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("case", [(1, 4, 4), (1, 5, 13), (2, 14, 14)], ids=lambda c: "N%d_%dx%d" % c)
+def test_four_chunks_are_not_split_where_that_loses(case, dtype):
+    """C = 256, E = 1: groups only from 17 to 64 pixels; else the workspace
+    stays as it was."""
+    N, H, W = case
+    x, p = make_block(97, N, H, W, 256, 1, 3, dtype)
+    say("E = 1", case, dtype)
+    y, written = run(x.cuda(), to_dev(p), 8 * N * H * W * 1024)
+    assert written == 0
+    assert_close(y.cpu(), oracle_block(x, p), what="E = 1 %s %s" % (case, dtype),
+                 diag=DIAG_F16 if dtype == "f16" else None)
+
+
 @pytest.mark.parametrize("N", [2, 24])
 def test_stage_too_wide_for_the_two_launch_block_keeps_its_groups(N):
     """C = 512, E = 8 in fp16: the hidden layer is split over four groups
