@@ -337,7 +337,8 @@ def _workspace(x: torch.Tensor, ws, need: int, stream):
 # The hidden-layer split of wide blocks over few pixels keeps fp32 partials in
 # scratch memory.  Above SPLIT_PIXELS there are tiles enough for every CU,
 # beyond SPLIT_HIDDEN channels the kernel's LDS has no room, and SPLIT_BYTES is
-# what the library uses at most.
+# what the library uses at most; one expansion factor of C = 256 makes groups
+# worth their reduction only between 17 and 64 pixels.
 SPLIT_PIXELS, SPLIT_HIDDEN, SPLIT_BYTES = 4096, 3584, 16 << 20
 
 
@@ -346,19 +347,23 @@ def _split_bytes(x: torch.Tensor, hidden: int) -> int:
     the shape has none)."""
     N, H, W, C = x.shape
     pixels = N * H * W
-    if pixels > SPLIT_PIXELS or C < 256 or hidden > SPLIT_HIDDEN:
+    if pixels > SPLIT_PIXELS or C < 256 or hidden > SPLIT_HIDDEN or (hidden == 256 and not 16 < pixels <= 64):
         return 0
     return min(SPLIT_BYTES, 64 * pixels * C * 4)
 
 
+def _torch_stream(x: torch.Tensor, stream):
+    """`stream`, any object with a cuda_stream handle, as torch's own kind of
+    stream (None: None)."""
+    if stream is None or isinstance(stream, torch.cuda.Stream):
+        return stream
+    return torch.cuda.ExternalStream(stream.cuda_stream, device=x.device)
+
+
 def _allocating_for(x: torch.Tensor, stream):
-    """A context in which torch allocates from the pool of `stream`, any object
-    with a cuda_stream handle (None: the current stream's, as without)."""
-    if stream is None:
-        return contextlib.nullcontext()
-    if not isinstance(stream, torch.cuda.Stream):
-        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=x.device)
-    return torch.cuda.stream(stream)
+    """A context in which torch allocates from the pool of `stream` (None: the
+    current stream's, as without)."""
+    return contextlib.nullcontext() if stream is None else torch.cuda.stream(_torch_stream(x, stream))
 
 
 def _new(x: torch.Tensor, shape, stream):
@@ -396,36 +401,80 @@ def _prepare_block(x: torch.Tensor, p: dict, act: str, out, stream):
     return y, bp, keep, _block_shape(x, p)
 
 
+def _block_call(x, y, bp, dims, act, split, stream):
+    """One block: with its hidden layer split over scratch memory of `split`
+    bytes, or (0) by the configuration that the library has cached or its
+    default."""
+    N, H, W, C, E, k = dims
+    a = (N, H, W, C, E, k, DTYPES[x.dtype], ACTS[act], _stream(stream))
+    if split:
+        ws = _scratch(x, split, stream)
+        _check(lib().cf_stage_forward(x.data_ptr(), y.data_ptr(), ws.data_ptr(), split, bp, 1, *a))
+    else:
+        _check(lib().cf_block_forward(x.data_ptr(), y.data_ptr(), bp, *a))
+
+
+# Blocks that block_autotune found faster without the hidden split, which takes
+# scratch memory and so is not among the configurations that the library times:
+# (device, N, H, W, C, E, k, dtype, act), as the library keys its own choices.
+_UNSPLIT = set()
+
+
+def _tune_key(x, dims, act):
+    return (x.device.index, *dims, x.dtype, act)
+
+
 def block_forward(x: torch.Tensor, p: dict, act: str = "gelu", out: torch.Tensor | None = None,
                   stream=None) -> torch.Tensor:
     """Fused ConvFirst block: y = x + FFN(dwconv(x)).  A wide block over few
-    pixels takes scratch memory for its hidden split from torch's allocator."""
+    pixels takes scratch memory for its hidden split from torch's allocator
+    (stage_forward with the one block and a workspace does not), unless
+    block_autotune found it faster without."""
     f = _block_fast(x, p) if act in ACTS else None
     yf = None if f is None else _y_fast(x, out, f[:4], stream)
     if yf is not None:
-        (N, H, W, C, dt, xp, E, k, bp), (y, yp) = f, yf
+        (N, H, W, C, _, _, E, k, bp), (y, _) = f, yf
     else:
         y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out, stream)
-        dt, xp, yp, bp = DTYPES[x.dtype], x.data_ptr(), y.data_ptr(), ctypes.byref(bp)
-    ws = _scratch(x, _split_bytes(x, E * C), stream)
-    if ws is not None:  # the hidden split beats every configuration the tuner knows
-        _check(lib().cf_stage_forward(xp, yp, ws.data_ptr(), ws.numel(), bp, 1, N, H, W, C, E, k, dt, ACTS[act],
-                                      _stream(stream)))
-    else:
-        _check(lib().cf_block_forward(xp, yp, bp, N, H, W, C, E, k, dt, ACTS[act], _stream(stream)))
+        bp = ctypes.byref(bp)
+    split, dims = _split_bytes(x, E * C), (N, H, W, C, E, k)
+    if split and _UNSPLIT and _tune_key(x, dims, act) in _UNSPLIT:
+        split = 0
+    _block_call(x, y, bp, dims, act, split, stream)
     return y
 
 
 def block_autotune(x: torch.Tensor, p: dict, act: str = "gelu", out: torch.Tensor | None = None,
                    stream=None) -> torch.Tensor:
-    """Time every kernel configuration that applies to this block shape, cache
-    the fastest for later block_forward calls (those with a hidden split keep
-    it), return the block's output."""
-    y, bp, keep, (N, H, W, C, E, k) = _prepare_block(x, p, act, out, stream)
-    _check(lib().cf_block_autotune(_ptr(x), _ptr(y), ctypes.byref(bp), N, H, W, C, E, k,
+    """Time every kernel configuration that applies to this block shape, the
+    hidden split among them, cache the fastest for later block_forward calls,
+    return the block's output."""
+    y, bp, keep, dims = _prepare_block(x, p, act, out, stream)
+    N, H, W, C, E, k = dims
+    bp, split = ctypes.byref(bp), _split_bytes(x, E * C)
+    _check(lib().cf_block_autotune(_ptr(x), _ptr(y), bp, N, H, W, C, E, k,
                                    DTYPES[x.dtype], ACTS[act], _stream(stream)))
-    if _split_bytes(x, E * C):
-        return block_forward(x, p, act, out=y, stream=stream)
+    if not split:
+        return y
+
+    on = _torch_stream(x, stream)
+
+    def time(nbytes):  # one untimed call, then three timed ones
+        _block_call(x, y, bp, dims, act, nbytes, stream)
+        ends = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        ends[0].record(on)
+        for _ in range(3):
+            _block_call(x, y, bp, dims, act, nbytes, stream)
+        ends[1].record(on)
+        ends[1].synchronize()
+        return ends[0].elapsed_time(ends[1])
+
+    key = _tune_key(x, dims, act)
+    if time(0) < time(split):
+        _UNSPLIT.add(key)
+        _block_call(x, y, bp, dims, act, 0, stream)
+    else:
+        _UNSPLIT.discard(key)
     return y
 
 

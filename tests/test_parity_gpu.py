@@ -349,3 +349,36 @@ def test_wide_blocks_depend_on_neither_tile_nor_batch(dtype):
     whole = run(100)
     for n in (1, 40, 60):
         assert torch.equal(run(n), whole[:n])
+
+
+@pytest.mark.parametrize("case", [(256, 2, 3, 16, 14, 14, "f16"), (256, 4, 3, 1, 7, 7, "bf16"),
+                                  (512, 4, 3, 1, 7, 7, "f16")], ids=lambda c: "C%d_E%d_k%d_N%d_%dx%d_%s" % c)
+def test_block_forward_takes_what_the_autotuner_chose(case, monkeypatch):
+    """The tuner times the hidden split against the library's configurations,
+    and block_forward gives the bits of the one that was faster: here with
+    either side made the faster one."""
+    import ctypes
+    C, E, k, N, H, W, dtype = case
+    say("autotuned split", case)
+    x, p = make_block(43, N, H, W, C, E, k, dtype)
+    xd, pd = x.cuda(), to_dev(p)
+    split = cf._split_bytes(xd, E * C)
+    assert split
+    monkeypatch.setattr(cf, "_UNSPLIT", set())
+    y = cf.block_autotune(xd, pd)
+    assert torch.equal(y, cf.block_forward(xd, pd))
+    keep = []
+    bp = cf._block_struct(xd, pd, keep)
+    alone, groups = torch.empty_like(xd), torch.empty_like(xd)
+    cf._block_call(xd, alone, ctypes.byref(bp), (N, H, W, C, E, k), "gelu", 0, None)
+    cf._block_call(xd, groups, ctypes.byref(bp), (N, H, W, C, E, k), "gelu", split, None)
+    assert not torch.equal(alone, groups)
+    call = cf._block_call
+    for slow, want in ((0, groups), (split, alone)):
+        def slowed(x_, y_, bp_, dims, act, nbytes, stream):
+            for _ in range(30 if nbytes == slow else 1):
+                call(x_, y_, bp_, dims, act, nbytes, stream)
+        monkeypatch.setattr(cf, "_block_call", slowed)
+        y = cf.block_autotune(xd, pd)
+        monkeypatch.setattr(cf, "_block_call", call)
+        assert torch.equal(y, want) and torch.equal(cf.block_forward(xd, pd), want)

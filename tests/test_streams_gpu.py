@@ -70,3 +70,19 @@ def test_call_on_a_side_stream(name, out, monkeypatch):
     assert torch.equal(got, want)
     assert at and all(s == side for s in at), at
     assert torch.cuda.current_stream() == torch.cuda.default_stream()
+
+
+def test_any_object_with_a_stream_handle_will_do():
+    class Handle:
+        def __init__(self, stream):
+            self.cuda_stream = stream.cuda_stream
+
+    side = torch.cuda.Stream()
+    x, p = make_block(95, 1, 7, 7, 256, 4, 3)
+    x, p = x.cuda(), to_dev(p)
+    want = cf.block_forward(x, p).clone()
+    torch.cuda.synchronize()
+    for call in (cf.block_forward, cf.block_autotune, lambda x, p, stream: cf.stage_forward(x, [p], stream=stream)):
+        got = call(x, p, stream=Handle(side))
+        torch.cuda.current_stream().wait_stream(side)
+        assert (got - want).abs().max() <= 2e-2 * want.abs().max()
