@@ -349,6 +349,8 @@ def _split_bytes(x: torch.Tensor, hidden: int) -> int:
     pixels = N * H * W
     if pixels > SPLIT_PIXELS or C < 256 or hidden > SPLIT_HIDDEN or (hidden == 256 and not 16 < pixels <= 64):
         return 0
+    if C == 512 and x.dtype == torch.float16 and pixels >= 4096 and 2 * pixels * (2 * C + hidden) <= SPLIT_BYTES:
+        return 0  # room for the library's layer-by-layer path, which is for stages
     return min(SPLIT_BYTES, 64 * pixels * C * 4)
 
 

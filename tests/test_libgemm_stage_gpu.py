@@ -14,7 +14,7 @@ import oracle
 import paper_2404_03617_amd as cf
 from paper_2404_03617_amd import synth
 
-from _util import DIAG_F16, assert_close, to_dev
+from _util import DIAG_F16, assert_close, make_block, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -78,3 +78,22 @@ def test_c512_layer_by_layer_graph_replays_match_eager():
         assert torch.equal(out, y_eager), "replay %d" % i
         cf.stage_forward(xd, bd)  # eager work between replays
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("E", [1, 2])
+def test_a_single_block_does_not_take_the_library_path(E):
+    """At 4096 pixels the scratch of block_forward's hidden split would have
+    been room enough for the layer-by-layer path, which creates library plans
+    and takes the library's GELU: a single block keeps the kernels of
+    cf_block_forward."""
+    import ctypes
+    N, H, W, C, k = 64, 8, 8, 512, 3
+    x, p = make_block(66, N, H, W, C, E, k, "f16")
+    xd, pd = x.cuda(), to_dev(p)
+    keep = []
+    bp = cf._block_struct(xd, pd, keep)
+    want = torch.empty_like(xd)
+    cf._check(cf.lib().cf_block_forward(xd.data_ptr(), want.data_ptr(), ctypes.byref(bp), N, H, W, C, E, k,
+                                        cf.DTYPES[xd.dtype], 0, None))
+    torch.cuda.synchronize()
+    assert torch.equal(cf.block_forward(xd, pd), want)
