@@ -503,6 +503,12 @@ def _prepare_stage(x: torch.Tensor, blocks: list, out, stream):
     return _out(x, out, stream), (_BlockParams * len(blocks))(*structs), dims.pop()
 
 
+def _ping_pong_bytes(x: torch.Tensor, depth: int) -> int:
+    """The least workspace of a stage: the buffer that its blocks' outputs
+    alternate with."""
+    return 0 if depth == 1 else (x.numel() * 2 + 255) // 256 * 256
+
+
 def stage_forward(x: torch.Tensor, blocks: list, act: str = "gelu", out=None, ws=None,
                   stream=None) -> torch.Tensor:
     """`len(blocks)` fused blocks of one shape, ping-ponging through ws."""
@@ -513,7 +519,10 @@ def stage_forward(x: torch.Tensor, blocks: list, act: str = "gelu", out=None, ws
     y, arr, (N, H, W, C, E, k) = _prepare_stage(x, blocks, out, stream)
     L = lib()
     need = L.cf_stage_workspace_bytes(len(blocks), N, H, W, C, DTYPES[x.dtype])
-    ws = _scratch(x, need + _split_bytes(x, E * C), stream) if ws is None else _workspace(x, ws, need, stream)
+    if ws is None:
+        ws = _scratch(x, need + _split_bytes(x, E * C), stream)
+    else:  # at C = 256 what is recommended beyond the ping-pong buffer is for hidden groups, and optional
+        ws = _workspace(x, ws, min(need, _ping_pong_bytes(x, len(blocks))) if C == 256 else need, stream)
     _check(L.cf_stage_forward(_ptr(x), _ptr(y), _ptr(ws), 0 if ws is None else ws.numel(),
                               arr, len(blocks), N, H, W, C, E, k, DTYPES[x.dtype], ACTS[act],
                               _stream(stream)))

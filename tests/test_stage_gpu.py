@@ -69,3 +69,28 @@ def test_microbatch_stage_full_size_first_stage_of_the_stack():
     y = cf.stage_forward_microbatch(x.cuda(), [to_dev(b) for b in blocks])
     torch.cuda.synchronize()
     assert_close(y.cpu(), oracle_stage(x, blocks), what="stage 1 micro-batched")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_stage_takes_the_least_workspace(dtype):
+    """The room for hidden groups that cf_stage_workspace_bytes recommends at
+    C = 256 is no requirement: the ping-pong buffer will do, for one block an
+    empty workspace.  Less than that is refused, as is less than recommended at
+    C = 512 in fp16."""
+    N, H, W, C, E, k = 2, 9, 8, 256, 2, 3
+    x, blocks = stage(82, 2, N, H, W, C, E, k, dtype)
+    xd, bd = x.cuda(), [to_dev(b) for b in blocks]
+    least = N * H * W * C * 2
+    assert cf.lib().cf_stage_workspace_bytes(2, N, H, W, C, cf.DTYPES[x.dtype]) > least
+    for n, bytes_ in ((2, least), (2, least + 4 * least), (1, 0), (1, 256)):
+        say("least workspace", dtype, n, bytes_)
+        ws = torch.empty(bytes_, dtype=torch.uint8, device="cuda")
+        y = cf.stage_forward(xd, bd[:n], ws=ws)
+        torch.cuda.synchronize()
+        assert_close(y.cpu(), oracle_stage(x, blocks[:n]), what="least workspace %s %d" % (dtype, bytes_))
+    with pytest.raises(ValueError, match="needs"):
+        cf.stage_forward(xd, bd, ws=torch.empty(least - 1, dtype=torch.uint8, device="cuda"))
+    if dtype == "f16":
+        x, blocks = stage(83, 1, 1, 7, 7, 512, 2, 3, dtype)
+        with pytest.raises(ValueError, match="needs"):
+            cf.stage_forward(x.cuda(), [to_dev(b) for b in blocks], ws=torch.empty(256, dtype=torch.uint8, device="cuda"))
