@@ -42,7 +42,7 @@
 // Bound by the chain of the five steps at eight or sixteen waves per CU.  A wave working
 // alone on units of 16 pixels (the earlier form of this kernel) left room for
 // four waves in the LDS at C = 48 and read every weight from L2 for each unit:
-// N = 128, 64 x 64, C = 48, R = 288, K = 64, fp16: 151 us then, 89 us now.
+// N = 128, 64 x 64, C = 48, R = 288, K = 64, fp16: 151 us then, 85 us now.
 #include "cf_device.h"
 #include "cf_kernels.h"
 
@@ -302,8 +302,11 @@ struct Kern {
             }
             __syncthreads();
 
-            // 4. expand: hidden tiles wv, wv + 8, ..
+            // 4. expand: hidden tiles wv, wv + 8, ..; eight zeros behind each
+            //    pixel's hidden values, for the project's K steps past R
             {
+                if (tid < 16 * TR)
+                    *reinterpret_cast<u32x4 *>(Hd + (uint32_t)tid * PH + (uint32_t)R * 2) = u32x4{0u, 0u, 0u, 0u};
                 u32x4 zf[TR][KS];
 #pragma unroll
                 for (int t = 0; t < TR; t++)
@@ -377,18 +380,12 @@ struct Kern {
                                 w[k] = ld16(wr + min(32 * (KB * b + k) + 8 * lp, R - 8));
                     };
                     auto use = [&](int b, const u32x4 (&w)[KB]) {
-                        // a K step past R (R % 32 == 16, or the batch's end) meets zeros
+                        // a K step past R (R % 32 == 16, or the batch's end) repeats
+                        // weights and meets the zeros behind the pixel's hidden values
                         u32x4 wf[KB];
 #pragma unroll
-                        for (int k = 0; k < KB; k++) {
+                        for (int k = 0; k < KB; k++)
                             wf[k] = WL ? w[k] : permute(pidx, w[k]);
-                            if (32 * (KB * b + k) + 32 > R) {  // uniform
-                                const bool in = 32 * (KB * b + k) + 8 * q < R;
-#pragma unroll
-                                for (int d = 0; d < 4; d++)
-                                    wf[k][d] = in ? wf[k][d] : 0u;
-                            }
-                        }
 #pragma unroll
                         for (int t = 0; t < TR; t++)
                             if (t >= ta && t < tb) {  // uniform
@@ -396,7 +393,7 @@ struct Kern {
                                 const uint8_t *hp = Hd + (uint32_t)(16 * t + jl) * PH;
 #pragma unroll
                                 for (int k = 0; k < KB; k++)
-                                    hv[k] = *reinterpret_cast<const u32x4 *>(hp + min(32 * (KB * b + k) + 8 * q, R - 8) * 2);
+                                    hv[k] = *reinterpret_cast<const u32x4 *>(hp + min(32 * (KB * b + k) + 8 * q, R) * 2);
 #pragma unroll
                                 for (int k = 0; k < KB; k++)
                                     acc[t] = T::mfma(wf[k], hv[k], acc[t]);

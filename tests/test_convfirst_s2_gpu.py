@@ -133,3 +133,29 @@ def test_convfirst_s2_every_tile_plan(case):
     y = run(x, p)
     pick = sorted({0, N // 2, N - 1})
     assert_close(y.cpu()[pick], ref(x[pick], p), what="convfirst_s2 plan %s" % (case,), diag=DIAG_F16)
+
+
+@pytest.mark.parametrize("case", [(16, 48, 32, 2, 12, 40), (48, 272, 64, 90, 14, 70), (48, 288, 64, 2, 14, 70)],
+                         ids=lambda c: "C%d_R%d_K%d_N%d_%dx%d" % c)
+def test_convfirst_s2_infinite_hidden_values_stay_infinite(case):
+    """The last eight hidden channels overflow fp16 at some pixels: with their
+    project weights positive the outputs there are +inf, whether the K steps
+    past R (R % 32 == 16, or the end of a batch of steps) repeat them or not,
+    and the outputs elsewhere are what they are without the overflow."""
+    C, R, K, N, H, W = case
+    say("convfirst_s2 overflow", case)
+    x, p = make(287, N, H, W, C, R, K, scales="none", bias_std=None)
+    p["w2"][:, R - 8:] = p["w2"][:, R - 8:].abs().clamp_min(2.0 ** -6)
+    p["s1"] = torch.ones(R)
+    calm = run(x, p)
+    p["s1"][R - 8:] = 3.0e5
+    y = run(x, p)
+    assert not y.isnan().any()
+    hit = y.isinf()
+    assert (y[hit] > 0).all() and 0.05 < hit.float().mean() < 1.0
+    # pixels none of whose overflowing channels is positive
+    p["w2"][:, R - 8:] = 0
+    p["s1"][R - 8:] = 1.0
+    none = run(x, p)
+    zero = (calm == none).all(-1)
+    assert not hit[zero].any() and torch.equal(y[zero], calm[zero])
