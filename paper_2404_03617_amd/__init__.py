@@ -411,9 +411,10 @@ def _block_call(x, y, bp, dims, act, split, stream):
     a = (N, H, W, C, E, k, DTYPES[x.dtype], ACTS[act], _stream(stream))
     if split:
         ws = _scratch(x, split, stream)
-        _check(lib().cf_stage_forward(x.data_ptr(), y.data_ptr(), ws.data_ptr(), split, bp, 1, *a))
-    else:
-        _check(lib().cf_block_forward(x.data_ptr(), y.data_ptr(), bp, *a))
+        status = lib().cf_stage_forward(x.data_ptr(), y.data_ptr(), ws.data_ptr(), split, bp, 1, *a)
+        if status not in (CF_ERR_INVALID, CF_ERR_UNSUPPORTED):  # cf_block_forward says what is wrong
+            return _check(status)
+    _check(lib().cf_block_forward(x.data_ptr(), y.data_ptr(), bp, *a))
 
 
 # Blocks that block_autotune found faster without the hidden split, which takes

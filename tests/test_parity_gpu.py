@@ -382,3 +382,12 @@ def test_block_forward_takes_what_the_autotuner_chose(case, monkeypatch):
         y = cf.block_autotune(xd, pd)
         monkeypatch.setattr(cf, "_block_call", call)
         assert torch.equal(y, want) and torch.equal(cf.block_forward(xd, pd), want)
+
+
+def test_a_refused_block_is_named_by_its_own_entry_point():
+    """A shape without a kernel (the tile of C = 512 fp16 over rows of 14 pixels),
+    few enough pixels for the hidden split."""
+    x, p = make_block(44, 1, 14, 14, 512, 4, 3, "f16")
+    with pytest.raises(cf.CFError, match="cf_block_forward: tile") as ei:
+        cf.block_forward(x.cuda(), to_dev(p))
+    assert ei.value.status == cf.CF_ERR_UNSUPPORTED
