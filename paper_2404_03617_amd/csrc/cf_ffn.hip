@@ -290,7 +290,7 @@ hipError_t block(const void *x, void *y, const BlockW &w, const Shape &s, int gr
 bool ffn_applies(const Shape &s) {
     const int64_t P = (int64_t)s.N * s.H * s.W;
     return ((s.C == 128 && s.bf16) || (s.C == 256 && (s.bf16 || s.k >= 5 || P <= ffn::ROUND_PIXELS)) || s.C == 512) &&
-           P < ((int64_t)1 << 31) - 4096 &&
+           P < ((int64_t)1 << 31) - 4096 && ffn::dw_launchable((int64_t)s.N * s.H, s.W, s.C) &&
            ffn::lds_bytes(s.C, s.E * s.C) <= (s.C == 128 ? 80u : 160u) * 1024;
 }
 

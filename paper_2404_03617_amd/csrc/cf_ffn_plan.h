@@ -1,6 +1,5 @@
-// cf_ffn_plan.h -- host arithmetic of the hidden groups of the two-launch wide
-// block (cf_ffn.h), in plain C++ so that a test can walk through it without a
-// GPU.
+// cf_ffn_plan.h -- host arithmetic of the two-launch wide block (cf_ffn.h), in
+// plain C++ so that a test can walk through it without a GPU.
 #pragma once
 
 #include <stddef.h>
@@ -26,6 +25,15 @@ constexpr int filled_groups(int chunks, int g) {
 constexpr int fitting_groups(int chunks, int want, size_t one, size_t bytes) {
     return filled_groups(chunks, (size_t)want * one <= bytes ? want : (int)(bytes / one));
 }
+
+// Threads of the depth-wise launch over rows of W pixels: one for 8 channels of
+// up to four (or seven, when that makes fewer strips) neighbouring pixels, in
+// workgroups of 256.  A launch holds fewer than 2^32: images of one or two
+// columns reach that at 64 and 128 GiB.
+constexpr uint64_t dw_threads(int64_t rows, int W, int C) {
+    return ((uint64_t)rows * ((W + 3) / 4) * (C / 8) + 255) / 256 * 256;
+}
+constexpr bool dw_launchable(int64_t rows, int W, int C) { return dw_threads(rows, W, C) < (uint64_t)1 << 32; }
 
 }  // namespace ffn
 }  // namespace cf

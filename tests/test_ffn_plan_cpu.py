@@ -40,3 +40,36 @@ def test_every_group_that_is_counted_holds_chunks(tmp_path):
                 }
             }
     """)
+
+
+def test_depthwise_launches_stay_below_the_thread_limit(tmp_path):
+    """Every call that the two-launch block takes has a depth-wise grid of
+    fewer than 2^32 threads, by the kernel's own count (strips of four or
+    seven pixels, C / 8 threads each, 256 to a workgroup), up to the 2^31 pixels
+    that the entry points take; what it takes of narrow images ends at 64 GiB
+    for one column and 128 GiB for two."""
+    run_cpp(tmp_path, """
+    const int Cs[] = {128, 256, 512};
+    for (int C : Cs)
+        for (int W = 1; W <= 600; W++)
+            for (int64_t P = 1; P < (int64_t)1 << 31; P += P / 3 + 1) {
+                const int64_t rows = P / W;
+                if (rows < 1 || !dw_launchable(rows, W, C))
+                    continue;
+                const bool seven = (W + 6) / 7 * 7 <= (W + 3) / 4 * 4;
+                for (int tw = 4; tw <= (seven ? 7 : 4); tw += 3) {
+                    const int64_t strips = rows * ((W + tw - 1) / tw), per = 256 / (C / 8);
+                    const int64_t threads = (strips + per - 1) / per * 256;
+                    if (threads >= (int64_t)1 << 32 || strips >= (int64_t)1 << 31) {
+                        printf("C %d W %d rows %lld: %lld threads\\n", C, W, (long long)rows, (long long)threads);
+                        return 1;
+                    }
+                }
+            }
+    for (int C : Cs) {
+        const int64_t one = ((int64_t)1 << 36) / (2 * C), two = ((int64_t)1 << 37) / (4 * C);
+        if (dw_launchable(one, 1, C) || !dw_launchable(one - 64, 1, C) || dw_launchable(two, 2, C) ||
+            !dw_launchable(two - 64, 2, C) || !dw_launchable(((int64_t)1 << 37) / (16 * C), 8, C))
+            return 2;
+    }
+    """)
