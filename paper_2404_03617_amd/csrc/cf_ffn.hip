@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void dw_pixel_kernel(DwArgs a) {
 }
 
 constexpr int64_t FEW_PIXELS = 4096;
-constexpr int64_t ROUND_PIXELS = 16384;  // one 64-pixel tile for each of 256 CUs
+int64_t round_pixels() { return (int64_t)64 * device_cu_count(); }  // one 64-pixel tile for each CU
 
 // TW = 0: one pixel per thread
 template <typename T, int KS, int TW>
@@ -242,13 +242,13 @@ hipError_t ffn(const Args &a, int C, int groups, bool f32, hipStream_t st) {
     if (C == 128)
         return ffn_launch<T, 128, 2, 2, ACT>(a, groups, st);
     // C = 256: the pixel tile grows with the batch, so that the weights are
-    // streamed as seldom as the CUs can be kept in one round: 32 pixels up to
-    // 8192 (30 images of 14 x 14 in bf16: 33.7 us against 36.0 and 49.9 with
+    // streamed as seldom as the CUs can be kept in one round (256 CUs): 32 pixels
+    // up to 8192 (30 images of 14 x 14 in bf16: 33.7 us against 36.0 and 49.9 with
     // 64 and 128), 64 up to 16384 (fp16, k = 5: 34.4 against 43.4 with 128),
     // then 128 (128 images, fp16: 51.3 against 58.9 with 64)
-    if (groups > 1 || a.P <= 8192)
+    if (groups > 1 || 2 * (int64_t)a.P <= round_pixels())
         return ffn_launch<T, 256, 1, 2, ACT>(a, groups, st);
-    if (a.P <= ROUND_PIXELS)
+    if (a.P <= round_pixels())
         return ffn_launch<T, 256, 1, 4, ACT>(a, groups, st);
     return ffn_launch<T, 256, 2, 4, ACT>(a, groups, st);
 }
@@ -289,7 +289,7 @@ hipError_t block(const void *x, void *y, const BlockW &w, const Shape &s, int gr
 // 160 (fp16) and 265 to 535 (bf16).  E up to 14 (7 at C = 512) by the LDS.
 bool ffn_applies(const Shape &s) {
     const int64_t P = (int64_t)s.N * s.H * s.W;
-    return ((s.C == 128 && s.bf16) || (s.C == 256 && (s.bf16 || s.k >= 5 || P <= ffn::ROUND_PIXELS)) || s.C == 512) &&
+    return ((s.C == 128 && s.bf16) || (s.C == 256 && (s.bf16 || s.k >= 5 || P <= ffn::round_pixels())) || s.C == 512) &&
            P < ((int64_t)1 << 31) - 4096 && ffn::dw_launchable((int64_t)s.N * s.H, s.W, s.C) &&
            ffn::lds_bytes(s.C, s.E * s.C) <= (s.C == 128 ? 80u : 160u) * 1024;
 }
