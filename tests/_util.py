@@ -49,3 +49,36 @@ def assert_close(gpu, ref, tol=TOL, what="", diag=None):
 def log_uniform(seed, tid, n, lo, hi):
     """Per-channel scales spread over several decades (folded batch norms)."""
     return synth.to_f32(np.exp(synth.draw_uniform(seed, tid, (n,), np.log(lo), np.log(hi))))
+
+
+def block_c(x, p, act="gelu"):
+    """cf_block_forward itself: no scratch memory, so no hidden groups (and for
+    a handful of pixels at C >= 128 the slice kernel)."""
+    import ctypes
+
+    import paper_2404_03617_amd as cf
+
+    N, H, W, C = x.shape
+    keep = []
+    bp = cf._block_struct(x, p, keep)
+    y = torch.empty_like(x)
+    cf._check(cf.lib().cf_block_forward(x.data_ptr(), y.data_ptr(), ctypes.byref(bp), N, H, W, C,
+                                        p["w1"].shape[0] // C, p["dw_w"].shape[0], cf.DTYPES[x.dtype], cf.ACTS[act],
+                                        torch.cuda.current_stream().cuda_stream))
+    return y
+
+
+RESERVED = 256 + 2048 * 128  # bytes at the start of an MBConv workspace that no call touches
+_PAD = 4096
+
+
+def guarded_ws(nbytes):
+    """An MBConv workspace of nbytes full of 0xA5, and as much behind it."""
+    return torch.full((nbytes + _PAD,), 0xA5, dtype=torch.uint8, device="cuda")[:nbytes]
+
+
+def untouched(ws):
+    """Whether the reserved bytes of a guarded_ws and those behind it are as
+    they were."""
+    whole = torch.empty(0, dtype=torch.uint8, device="cuda").set_(ws.untyped_storage())
+    return bool((whole[:RESERVED] == 0xA5).all()) and bool((whole[ws.numel():] == 0xA5).all())

@@ -15,7 +15,7 @@ import paper_2404_03617_amd as cf
 from paper_2404_03617_amd import synth
 from paper_2404_03617_amd.workloads import WORKLOADS
 
-from _util import DIAG_F16, TOL, assert_close, log_uniform, make_block, oracle_block, rel_err, to_dev
+from _util import DIAG_F16, TOL, assert_close, block_c, log_uniform, make_block, oracle_block, rel_err, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -317,15 +317,23 @@ def test_wide_two_launch_blocks_match_oracle(case, dtype):
     y = cf.block_forward(xd, pd)
     torch.cuda.synchronize()
     assert_close(y.cpu()[pick], ref, what="wide %s %s" % (case, dtype), diag=diag)
-    # without room for hidden groups, and with room for three of them
+    # without room for hidden groups (the C entry point asks for none), and with
+    # room for three of them: partials behind the last group stay as they were
+    import ctypes
     P = N * H * W
+    keep = []
+    bp = cf._block_struct(xd, pd, keep)
+    chunks = E * C // (32 if C == 512 else 64)
     for groups in (0, 3):
-        ws = torch.empty(groups * P * C * 4 + 256, dtype=torch.uint8, device="cuda")
-        y1 = cf.stage_forward(xd, [pd], ws=ws) if cf.lib().cf_stage_workspace_bytes(
-            1, N, H, W, C, cf.DTYPES[x.dtype]) <= ws.numel() else None
+        ws = torch.full((groups * P * C * 4 + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+        y1 = torch.empty_like(xd)
+        cf._check(cf.lib().cf_stage_forward(xd.data_ptr(), y1.data_ptr(), ws.data_ptr(), ws.numel(), ctypes.byref(bp), 1,
+                                            N, H, W, C, E, k, cf.DTYPES[xd.dtype], 0, None))
         torch.cuda.synchronize()
-        if y1 is not None:
-            assert_close(y1.cpu()[pick], ref, what="wide %s %s groups %d" % (case, dtype, groups), diag=diag)
+        assert_close(y1.cpu()[pick], ref, what="wide %s %s groups %d" % (case, dtype, groups), diag=diag)
+        written = int((~ws[:groups * P * C * 4].view(torch.float32).view(groups, -1).isnan().any(1)).sum()) if groups else 0
+        split = groups and C != 128 and P <= 4096 and (C, E) != (256, 1)
+        assert written == (min(3, -(-chunks // -(-chunks // 3))) if split else 0), (written, groups)
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
@@ -391,3 +399,26 @@ def test_a_refused_block_is_named_by_its_own_entry_point():
     with pytest.raises(cf.CFError, match="cf_block_forward: tile") as ei:
         cf.block_forward(x.cuda(), to_dev(p))
     assert ei.value.status == cf.CF_ERR_UNSUPPORTED
+
+
+# Hidden layers too wide for the two-launch block's LDS: the single-launch
+# kernels that take them, through the C entry point.
+TOO_WIDE = [
+    # C, E, k, N, H, W, dtype
+    (256, 15, 5, 2, 9, 7, "f16"),    # wave pairs with DMA-fed weight buffers (C = 256)
+    (256, 15, 7, 1, 10, 11, "f16"),  # (same, 7 x 7)
+    (512, 8, 3, 2, 7, 7, "f16"),     # the streaming kernel without groups
+    (512, 8, 3, 2, 7, 7, "bf16"),    # the small-batch kernel writing y itself
+    (256, 15, 3, 2, 6, 7, "bf16"),   # the generic kernel
+    (128, 15, 3, 2, 9, 11, "bf16"),  # (same)
+]
+
+
+@pytest.mark.parametrize("case", TOO_WIDE, ids=lambda c: "C%d_E%d_k%d_N%d_%dx%d_%s" % c)
+def test_blocks_too_wide_for_the_two_launch_kernels_match_oracle(case):
+    C, E, k, N, H, W, dtype = case
+    say("too wide", case)
+    x, p = make_block(64, N, H, W, C, E, k, dtype)
+    y = block_c(x.cuda(), to_dev(p))
+    torch.cuda.synchronize()
+    assert_close(y.cpu(), oracle_block(x, p), what="too wide %s" % (case,), diag=DIAG_F16 if dtype == "f16" else None)

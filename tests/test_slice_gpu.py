@@ -1,7 +1,8 @@
 """Parity of the block for a handful of pixels (N*H*W <= 64, C = 128, 256,
 512) with the fp64 oracle.  cf_block_forward runs these shapes by default on
 one workgroup per 32 output channels, each recomputing the expand and summing
-its waves' projections in LDS (no workspace).
+its waves' projections in LDS (no workspace); block_forward does so at C = 128
+and elsewhere splits the hidden layer over scratch memory.  Both are tested.
 
 Gate: max |gpu - oracle| <= 2e-2 * max |oracle| over the whole output; fp16
 cases also meet DIAG_F16.  Covers one and two 32-pixel blocks (P = 1, 32, 33,
@@ -15,7 +16,7 @@ import torch
 
 import paper_2404_03617_amd as cf
 
-from _util import DIAG_F16, assert_close, make_block, oracle_block, to_dev
+from _util import DIAG_F16, assert_close, block_c, make_block, oracle_block, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -24,6 +25,8 @@ def say(*a):
     print(*a, flush=True)
     sys.stdout.flush()
 
+
+ENTRIES = (block_c, cf.block_forward)
 
 SHAPES = [
     # C, E, k, N, H, W
@@ -48,36 +51,38 @@ def test_slice_block_matches_oracle(case, dtype):
     x, p = make_block(71, N, H, W, C, E, k, dtype)
     xd, pd = x.cuda(), to_dev(p)
     for act in ("gelu", "relu", "none"):
-        y = cf.block_forward(xd, pd, act=act)
-        torch.cuda.synchronize()
-        assert_close(y, oracle_block(x, p, act), what="slice %s %s %s" % (case, dtype, act),
-                     diag=DIAG_F16 if dtype == "f16" else None)
+        for entry in ENTRIES:
+            y = entry(xd, pd, act=act)
+            torch.cuda.synchronize()
+            assert_close(y, oracle_block(x, p, act), what="slice %s %s %s %s" % (entry.__name__, case, dtype, act),
+                         diag=DIAG_F16 if dtype == "f16" else None)
 
 
 def test_slice_null_scales_and_biases():
     x, p = make_block(72, 1, 7, 7, 512, 4, 3, "bf16", scales="none", bias_std=None)
     assert all(p[k] is None for k in ("s0", "b0", "s1", "b1", "s2", "b2"))
-    y = cf.block_forward(x.cuda(), to_dev(p))
-    assert_close(y, oracle_block(x, p), what="slice null scale/bias")
+    for entry in ENTRIES:
+        assert_close(entry(x.cuda(), to_dev(p)), oracle_block(x, p), what="slice null scale/bias")
 
 
 def test_slice_zero_project_weights_pass_the_residual_exactly():
     x, p = make_block(73, 2, 4, 5, 256, 4, 3, "f16")
     p["w2"] = torch.zeros_like(p["w2"])
     p["b2"] = None
-    y = cf.block_forward(x.cuda(), to_dev(p))
-    assert torch.equal(y.cpu(), x)
+    for entry in ENTRIES:
+        assert torch.equal(entry(x.cuda(), to_dev(p)).cpu(), x)
 
 
-def test_slice_images_are_independent_and_deterministic():
+@pytest.mark.parametrize("entry", ENTRIES)
+def test_slice_images_are_independent_and_deterministic(entry):
     N, H, W, C, E, k = 4, 4, 4, 256, 4, 3
     x, p = make_block(74, N, H, W, C, E, k, "bf16")
     xd, pd = x.cuda(), to_dev(p)
-    y = cf.block_forward(xd, pd)
-    assert torch.equal(y, cf.block_forward(xd, pd))
+    y = entry(xd, pd)
+    assert torch.equal(y, entry(xd, pd))
     x2 = xd.clone()
     x2[1] = make_block(75, 1, H, W, C, E, k, "bf16")[0][0].cuda()
-    y2 = cf.block_forward(x2, pd)
+    y2 = entry(x2, pd)
     torch.cuda.synchronize()
     assert torch.equal(y[0], y2[0]) and torch.equal(y[2:], y2[2:])
     assert not torch.equal(y[1], y2[1])
