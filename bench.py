@@ -244,28 +244,20 @@ def mbconv_case(name: str, steps: int, warmup: int):
     ys = [torch.empty_like(xs[0]) for _ in range(nsets)]
     p = {kk: (None if v is None else v.cuda()) for kk, v in
          synth.mbconv_params(w["seed"], 0, C, E, R, w["dtype"]).items()}
-    ws = torch.zeros(cf.mbconv_workspace_bytes(N, H, W, C, E, R), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(cf.mbconv_workspace_bytes(N, H, W, C, E, R), dtype=torch.uint8, device="cuda")
     stream = torch.cuda.current_stream()
     t = _time(lambda i: cf.mbconv_forward(xs[i % nsets], p, out=ys[i % nsets], ws=ws), steps, warmup, stream)
-    # the other launch mode (the two launch alike)
-    te = _time(lambda i: cf.mbconv_forward(xs[i % nsets], p, out=ys[i % nsets], ws=ws, launch="exclusive"),
-               steps, warmup, stream)
-    torch.cuda.synchronize()
-    if int(ws[:4].view(torch.int32).item()) != 0:
-        raise RuntimeError("%s: the MBConv kernel wrote to the reserved workspace header" % name)
     flops = rl.mbconv_flops(N, H, W, C, E, R)
     nbytes = rl.mbconv_bytes_fused(N, H, W, C, E, R)
     return {"ms": round(t * 1e3, 4), "images_per_s": round(N / t, 1), "tflops": round(flops / t / 1e12, 1),
             "comp_eff": round(rl.comp_eff(flops, t), 4), "roofline": roofline_entry(flops, nbytes, t),
-            "exclusive_launch_ms": round(te * 1e3, 4), "exclusive_launch_comp_eff": round(rl.comp_eff(flops, te), 4),
             "paper_A5000_comp_eff": round(w["paper_pct"] / 100, 3)}
 
 
 def mbconv_s2_case(name: str, steps: int, warmup: int):
     """The stride-2 MBConv + SE block (BlurPool after the grouped conv, project
     to K at half resolution) at one of the 16 x 16 rows of the paper's speed
-    projections, batch 128: one cooperative launch per step, and the same
-    grid as an ordinary launch."""
+    projections, batch 128: one call (two launches) per step."""
     w = MBCONV_S2_WORKLOADS[name]
     N, H, W, C, E, R, K = w["N"], w["H"], w["W"], w["C"], w["E"], w["R"], w["K"]
     Ho, Wo = (H + 1) // 2, (W + 1) // 2
@@ -274,19 +266,13 @@ def mbconv_s2_case(name: str, steps: int, warmup: int):
     ys = [torch.empty((N, Ho, Wo, K), dtype=xs[0].dtype, device="cuda") for _ in range(nsets)]
     p = {kk: (None if v is None else v.cuda()) for kk, v in
          synth.mbconv_params(w["seed"], 0, C, E, R, w["dtype"], K=K).items()}
-    ws = torch.zeros(cf.mbconv_s2_workspace_bytes(N, H, W, C, E, R, K), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(cf.mbconv_s2_workspace_bytes(N, H, W, C, E, R, K), dtype=torch.uint8, device="cuda")
     stream = torch.cuda.current_stream()
     t = _time(lambda i: cf.mbconv_s2_forward(xs[i % nsets], p, out=ys[i % nsets], ws=ws), steps, warmup, stream)
-    te = _time(lambda i: cf.mbconv_s2_forward(xs[i % nsets], p, out=ys[i % nsets], ws=ws, launch="exclusive"),
-               steps, warmup, stream)
-    torch.cuda.synchronize()
-    if int(ws[:4].view(torch.int32).item()) != 0:
-        raise RuntimeError("%s: the MBConv kernel wrote to the reserved workspace header" % name)
     flops = rl.mbconv_s2_flops(N, H, W, C, E, R, K)
     nbytes = rl.mbconv_s2_bytes_fused(N, H, W, C, E, R, K)
     return {"ms": round(t * 1e3, 4), "images_per_s": round(N / t, 1), "tflops": round(flops / t / 1e12, 1),
             "comp_eff": round(rl.comp_eff(flops, t), 4), "roofline": roofline_entry(flops, nbytes, t),
-            "exclusive_launch_ms": round(te * 1e3, 4), "exclusive_launch_comp_eff": round(rl.comp_eff(flops, te), 4),
             "paper_projection_ms_A5000": w["paper_proj_ms"]}
 
 
@@ -597,8 +583,7 @@ def main():
                           "warmup": args.warmup, "ms_per_step": g["ms"], "higher_is_better": True,
                           "scaling": "weak", "vs_baseline": None, "dtype": "f16",
                           "data": "synthetic (seeded N(0,1) activations, N(0,1/fan_in) weights)",
-                          "config": cfg, "comp_eff": g["comp_eff"], "roofline": g["roofline"],
-                          "exclusive_launch_ms": g["exclusive_launch_ms"]}), flush=True)
+                          "config": cfg, "comp_eff": g["comp_eff"], "roofline": g["roofline"]}), flush=True)
         if args.calib_copy:
             calib_copy()
         return
@@ -617,8 +602,7 @@ def main():
                           "warmup": args.warmup, "ms_per_step": g["ms"], "higher_is_better": True,
                           "scaling": "weak", "vs_baseline": None, "dtype": "f16",
                           "data": "synthetic (seeded N(0,1) activations, N(0,1/fan_in) weights)",
-                          "config": cfg, "comp_eff": g["comp_eff"], "roofline": g["roofline"],
-                          **({"exclusive_launch_ms": g["exclusive_launch_ms"]} if mb else {})}), flush=True)
+                          "config": cfg, "comp_eff": g["comp_eff"], "roofline": g["roofline"]}), flush=True)
         if args.calib_copy:
             calib_copy()
         return

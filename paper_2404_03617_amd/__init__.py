@@ -905,7 +905,7 @@ def mbconv_s2_forward(x: torch.Tensor, p: dict, out=None, ws=None, launch: str =
     """The stride-2 MBConv block (Fig. f:mbconv with stride 2; Sec. 5.4): as
     mbconv_forward, then BlurPool with the Triangle-3 filter (reflect padding,
     stride 2) on the conv output, the squeeze over the down-sampled map, the
-    project to K channels and no residual, in one launch.  p as for
+    project to K channels and no residual, in two launches.  p as for
     mbconv_forward except w2 [K,E*C] and s3,b3 [K]; the result is
     [N, ceil(H/2), ceil(W/2), K] and must not overlap x.  ws as for
     mbconv_forward, sized by mbconv_s2_workspace_bytes()."""

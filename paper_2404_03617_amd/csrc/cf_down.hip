@@ -34,8 +34,8 @@ struct Args {
     uint32_t P;           // output pixels, < 2^31
     uint32_t tiles;       // pixel tiles of the whole call
     uint32_t first;       // this launch's first eight of them
-    int Ho, Wo, Cin, NO;
-    FastDiv divWo, divHo, divNy;
+    int Wo, Cin, NO;
+    FastDiv divWo, divNy;
 };
 
 constexpr uint32_t PITCH = 1056;
@@ -238,11 +238,10 @@ hipError_t launch_downsample(const void *x, void *y, const void *wd, const float
     a.y = (uint16_t *)y;
     a.scale = sd;
     a.bias = bd;
-    a.Ho = H / 2;
     a.Wo = W / 2;
     a.Cin = Cin;
     a.NO = Cout;
-    const int64_t P = (int64_t)N * a.Ho * a.Wo;
+    const int64_t P = (int64_t)N * (H / 2) * a.Wo;
     if (P >= ((int64_t)1 << 31))
         return hipErrorInvalidValue;
     a.P = (uint32_t)P;
