@@ -61,7 +61,7 @@ typedef enum { CF_F16 = 0, CF_BF16 = 1 } cf_dtype;
  * Gaussian-CDF form u * Phi(u).  The fused fp16 kernels evaluate it with a
  * packed-fp16 polynomial whose absolute error is below 3.4e-3 for |u| < 10
  * and zero beyond (it saturates to 0 and u); every other kernel, blocks with
- * hidden groups (cf_stage_forward) up to 1024 pixels among them, works in fp32 with an
+ * hidden groups (cf_stage_forward) up to 128 pixels among them, works in fp32 with an
  * error below 1e-7 max(1, |u|) (the kernel for N*H*W <= 64: 3e-7, by the erf of
  * Abramowitz & Stegun 7.1.26).
  * CF_ACT_NONE makes the block affine (used by tests). */
@@ -120,7 +120,7 @@ cf_status cf_block_forward(const void *x, void *y, const cf_block_params *p,
  * at C = 512 fp16 and E > 7 over as many as the recommended room holds.
  * With any number of groups results are identical up to fp32 summation order;
  * without, a C = 512 or C = 256 fp16 block above 64 pixels takes the packed
- * GELU polynomial (with groups, only above 1024 pixels) and for k >= 5 sums the
+ * GELU polynomial (with groups, only above 128 pixels) and for k >= 5 sums the
  * rows of the depth-wise window in fp16 (with groups in fp32).  Deterministic.
  * The library GEMMs are given no workspace of their own. */
 cf_status cf_stage_forward(const void *x, void *y, void *ws, size_t ws_bytes,

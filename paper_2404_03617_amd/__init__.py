@@ -337,8 +337,7 @@ def _workspace(x: torch.Tensor, ws, need: int, stream):
 # The hidden-layer split of wide blocks over few pixels keeps fp32 partials in
 # scratch memory.  Above SPLIT_PIXELS there are tiles enough for every CU,
 # beyond SPLIT_HIDDEN channels the kernel's LDS has no room, and SPLIT_BYTES is
-# what the library uses at most; one expansion factor of C = 256 makes groups
-# worth their reduction only between 17 and 64 pixels.
+# what the library uses at most; E = 1 at C = 256 makes no groups above 64 pixels.
 SPLIT_PIXELS, SPLIT_HIDDEN, SPLIT_BYTES = 4096, 3584, 16 << 20
 
 
@@ -347,7 +346,7 @@ def _split_bytes(x: torch.Tensor, hidden: int) -> int:
     the shape has none)."""
     N, H, W, C = x.shape
     pixels = N * H * W
-    if pixels > SPLIT_PIXELS or C < 256 or hidden > SPLIT_HIDDEN or (hidden == 256 and not 16 < pixels <= 64):
+    if pixels > SPLIT_PIXELS or C < 256 or hidden > SPLIT_HIDDEN or (hidden == 256 and pixels > 64):
         return 0
     if C == 512 and x.dtype == torch.float16 and pixels >= 4096 and 2 * pixels * (2 * C + hidden) <= SPLIT_BYTES:
         return 0  # room for the library's layer-by-layer path, which is for stages

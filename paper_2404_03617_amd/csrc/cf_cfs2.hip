@@ -42,7 +42,7 @@
 // Bound by the chain of the five steps at eight or sixteen waves per CU.  A wave working
 // alone on units of 16 pixels (the earlier form of this kernel) left room for
 // four waves in the LDS at C = 48 and read every weight from L2 for each unit:
-// N = 128, 64 x 64, C = 48, R = 288, K = 64, fp16: 151 us then, 85 us now.
+// N = 128, 64 x 64, C = 48, R = 288, K = 64, fp16: 151 us then, 84 us now.
 #include "cf_device.h"
 #include "cf_kernels.h"
 

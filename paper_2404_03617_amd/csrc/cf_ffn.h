@@ -15,7 +15,7 @@
 // pixel tile nor the position of a pixel in it.
 //
 // Few pixels: grid.y splits the chunks into groups; each writes an fp32
-// partial of s2 * project and the caller adds the groups in order.  Up to 1024
+// partial of s2 * project and the caller adds the groups in order.  Up to 128
 // pixels these launches are chains of latencies, and the activation is the fp32
 // GELU in fp16 too (ACT_GELU_F32): 7 x 7, C = 256 and 512, E = 4, fp16, relative
 // error 7.9e-4 with the packed polynomial, 2.6e-4 this way.

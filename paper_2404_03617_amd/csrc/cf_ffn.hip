@@ -299,15 +299,16 @@ bool ffn_applies(const Shape &s) {
 // captured graph, groups 1 / 2 / 4 / 8 / 16 / 32: 4 images of 14 x 14 at
 // C = 256 fp16 39.0 / 24.7 / 22.4 / 22.4 / 29.0 / - us; one image of 7 x 7 at
 // C = 512 bf16 64.8 / 60.7 / 37.2 / 28.3 / 24.8 / 24.3 us.  C = 128 gains
-// nothing (20.4 / 19.9 / 21.1 us for 4 images of 28 x 28 in bf16), nor do the
-// four chunks of C = 256, E = 1, whose groups are all prologue and reduction: k = 3
-// fp16, with groups / without (up to 64 pixels the slice kernel) 13.4 / 12.2 us
-// for 16 pixels, 14.3 / 16.5 for 49, 14.4 / 12.8 for 196, 22.6 / 16.8 for 3920.
+// nothing (20.4 / 19.9 / 21.1 us for 4 images of 28 x 28 in bf16).  At C = 256,
+// E = 1 four chunks are all prologue and reduction: k = 3 fp16, with groups /
+// without (up to 64 pixels the slice kernel, in blocks of 32) 11.6 / 11.9 us for 4
+// pixels, 13.3 / 12.2 for 16, 14.3 / 16.5 for 49, 14.4 / 12.8 for 196, 22.6 / 16.8
+// for 3920; k = 7 13.3 / 17.9 for 16.
 int ffn_groups(const Shape &s) {
     if (!ffn_applies(s) || s.C == 128)
         return 1;
     const int64_t P = (int64_t)s.N * s.H * s.W;
-    if (s.C == 256 && s.E == 1 && (P <= 16 || P > 64))
+    if (s.C == 256 && s.E == 1 && (P > 64 || (s.k <= 3 && P > 4 && P <= 32)))
         return 1;
     const int px = s.C == 256 ? 32 : 64;
     const int64_t tiles = (P + px - 1) / px, chunks = s.E * s.C / ffn::chunk(s.C);
@@ -324,14 +325,15 @@ int ffn_fitting_groups(const Shape &whole, size_t one, size_t bytes) {
     return g > 1 ? ffn::fitting_groups(whole.E * whole.C / ffn::chunk(whole.C), g, one, bytes) : 1;
 }
 
-// fp16 GELU of a block with groups.  The kernels of a handful of pixels
-// (cf_slice.hip, cf_small.hip) work in fp32, and so do the groups up to 1024
-// pixels, where it costs a launch of latencies little: 4 images of 14 x 14 at
-// C = 256 18.2 us with the packed polynomial, 18.4 with fp32; 49 pixels 13.7 and
-// 13.9, at C = 512 23.0 and 22.9.  Above, the polynomial of the larger batches:
-// 16 such images 26.6 and 27.5 us, 64 of 7 x 7 at C = 512 64.3 and 67.2.
+// fp16 GELU of a block with groups.  The kernels of a handful of pixels work in
+// fp32 (cf_slice.hip up to 64, cf_small.hip at C = 512 up to the some 70 that its
+// LDS holds), and so do the groups over them, where it costs a launch of
+// latencies little: 49 pixels at C = 256 13.7 us with the packed polynomial and
+// 13.9 with fp32, at C = 512 23.0 and 22.9.  Above, the polynomial of the larger
+// batches: 16 images of 14 x 14 at C = 256 26.6 and 27.5 us, 64 of 7 x 7 at C = 512
+// 64.3 and 67.2, 4 of them over four groups 33.4 and 36.2.
 int ffn_group_cfg(const Shape &whole) {
-    return (int64_t)whole.N * whole.H * whole.W <= 1024 ? CFG_FFN_F32 : CFG_FFN;
+    return (int64_t)whole.N * whole.H * whole.W <= 128 ? CFG_FFN_F32 : CFG_FFN;
 }
 
 hipError_t launch_ffn_block(const void *x, void *y, const BlockW &w, const Shape &s, int groups, float *part,
