@@ -86,3 +86,31 @@ def test_any_object_with_a_stream_handle_will_do():
         got = call(x, p, stream=Handle(side))
         torch.cuda.current_stream().wait_stream(side)
         assert (got - want).abs().max() <= 2e-2 * want.abs().max()
+
+
+@pytest.mark.parametrize("fork", [False, True], ids=["capture_stream", "forked_stream"])
+def test_calls_with_a_stream_inside_a_capture(fork):
+    """A call whose stream is the one being captured, or one forked from it:
+    scratch memory and a new output come from the graph's pool, and every
+    replay gives what the eager call gives for the input at that time."""
+    x, p = make_block(94, 4, 14, 14, 256, 4, 3)
+    xd, pd = x.cuda(), to_dev(p)
+    inputs = [xd.clone(), synth.activations(92, 4, 14, 14, 256).cuda()]
+    refs = [cf.block_forward(v, pd).clone() for v in inputs]
+    own, side = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=own):
+        on = side if fork else own
+        if fork:
+            side.wait_stream(own)
+        y = cf.block_forward(xd, pd, stream=on)
+        z = cf.stage_forward(xd, [pd, pd], stream=on)
+        if fork:
+            own.wait_stream(side)
+    for i in (0, 1, 1, 0):
+        xd.copy_(inputs[i])
+        g.replay()
+        other = cf.stage_forward(inputs[i], [pd, pd])
+        torch.cuda.synchronize()
+        assert torch.equal(y, refs[i]) and torch.equal(z, other), "replay of input %d" % i
